@@ -39,6 +39,12 @@ namespace sigk {
 template <int P, int D>
 constexpr int ckpt_chunk = (P >= 10 && P <= 20 && D <= 16) ? 64 : 32;
 
+template <int P, int D>
+constexpr int ckpt_ring = ckpt_chunk<P, D> == 64 ? chunk64_ring(P, D) : ring_cols(P);
+// Columns per Neumann depth it records.
+template <int P, int D>
+constexpr int ckpt_depth_cols = inc_chunk<ckpt_chunk<P, D>, ckpt_ring<P, D>>;
+
 // Modes: kModeTable, the checkpointing sweep of a batch (snap: per-strip
 // frontier rows); kModeBlock, the checkpointing sweep of the blocks of one
 // anti-diagonal (snap: per-slot frontier rows; strip 0 reads its bottom line,
@@ -49,7 +55,7 @@ template <int P, int D>
 __global__ void __launch_bounds__(kWave)
     __attribute__((amdgpu_waves_per_eu(P <= 5 && D <= 8 ? 3 : 1))) ckpt_kernel(FwdArgs a,
                                                                               double* snap) {
-    constexpr int CH = ckpt_chunk<P, D>, RB = CH == 64 ? 128 : ring_cols(P);
+    constexpr int CH = ckpt_chunk<P, D>, RB = ckpt_ring<P, D>;
     __shared__ LdsStrip<P, D, CH, RB> L;
     Acc acc;
     const int lane = lane_id();
@@ -163,26 +169,6 @@ struct SegScratch {
     __device__ __forceinline__ double load(int row) const {
         return __builtin_bit_cast(
             double, __builtin_amdgcn_raw_buffer_load_b64(r, lane_id() * 8, row * (kWave * 8), 0));
-    }
-};
-
-// Byte offset of a lane's slot in a ring of ARB columns, stepped one column
-// at a time (two or three vector instructions instead of a division).
-template <int ARB>
-struct RingPos {
-    unsigned b;
-    __device__ __forceinline__ void set(int col) { b = (unsigned)ring_slot_of<ARB>(col) * 8u; }
-    __device__ __forceinline__ void next() {
-        if constexpr ((ARB & (ARB - 1)) == 0)
-            b = (b + 8u) & (unsigned)((ARB - 1) * 8);
-        else
-            b = b + 8u == (unsigned)(ARB * 8) ? 0u : b + 8u;
-    }
-    __device__ __forceinline__ void prev() {
-        if constexpr ((ARB & (ARB - 1)) == 0)
-            b = (b - 8u) & (unsigned)((ARB - 1) * 8);
-        else
-            b = b == 0u ? (unsigned)((ARB - 1) * 8) : b - 8u;
     }
 };
 
@@ -350,8 +336,7 @@ struct StripBwd {
 
     // depth record of the chunk of step t: depth + kRoughFlag if rough
     __device__ __forceinline__ int depth_at(int t) const {
-        const int CKCH = ckpt_chunk<P, D>;
-        const int k = min(t, m - 1) / CKCH;
+        const int k = min(t, m - 1) / ckpt_depth_cols<P, D>;
         return uniform((int)ckq[k]);
     }
 

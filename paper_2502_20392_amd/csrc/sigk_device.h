@@ -9,7 +9,7 @@
 namespace sigk {
 
 // ---------------------------------------------------------------- lanes
-__device__ __forceinline__ int lane_id() { return (int)threadIdx.x; }
+__device__ __forceinline__ int lane_id() { return (int)(threadIdx.x & 63u); }
 
 __device__ __forceinline__ uint64_t ballot(bool p) {
     return (uint64_t)__builtin_amdgcn_ballot_w64(p);

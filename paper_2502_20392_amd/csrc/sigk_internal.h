@@ -46,7 +46,7 @@ __host__ __device__ constexpr int chunk_cols(int P) { return 32; }
 // CU at D = 8); 64 columns (the most a 128-column ring allows: it holds
 // [c0-63, c0+chunk)) pay off at orders 4 and 5 with D = 8 (5-6% faster on
 // the long pair, order 6 ran 6% slower: a wave less per CU) and at orders
-// 10-20 with D <= 16, which run one wave per SIMD anyway (Gram workloads
+// 10-20 with D <= 16 (Gram workloads
 // 6-9% faster).  (The adjoint path keeps 32: there the wider buffers cost
 // more waves than the exchange saves.)
 __host__ __device__ constexpr int fwd_chunk_cols(int P, int D) {
@@ -59,6 +59,22 @@ __host__ __device__ constexpr int fwd_chunk_cols(int P, int D) {
 __host__ __device__ constexpr int ring_cols(int P) { return P <= 8 ? 128 : 96; }
 __host__ __device__ constexpr int fwd_ring_cols(int P, int D) {
     return fwd_chunk_cols(P, D) == 64 ? 128 : ring_cols(P);
+}
+// Columns of the ring in the plain and the checkpointing sweep of a variant
+// with 64-column chunks: orders 10-12 with 8 < d <= 16 load increments (and
+// set the Neumann depth) 32 columns at a time, so that two waves per SIMD fit
+// the CU's LDS.  The same in both sweeps: their values agree bit for bit.
+__host__ __device__ constexpr int chunk64_ring(int P, int D) {
+    return P >= 10 && P <= 12 && D == 16 ? 96 : 128;
+}
+// Waves per SIMD the forward sweep is compiled for.  One wave issues a vector
+// instruction every 5.25 cycles at best, two together one every 4 (measured on
+// chains of FP64 FMAs), so a second wave is worth a quarter of the time where
+// the map fits 256 registers without spills: orders 8-12 with d <= 16 (64 x 64
+// Gram, length 1024, d 16, order 10: 24.9 ms with one wave, 21.0 with two; at
+// order 20 it spills and 11.2 ms became 17.7).
+__host__ __device__ constexpr int fwd_waves(int P, int D) {
+    return P <= 6 && D <= 8 ? 3 : (P >= 8 && P <= 12 && D > 0 && D <= 16 ? 2 : 1);
 }
 // The other compiled frontier chunk of a (P, D > 0) forward variant: the
 // work-tile width (64 rows x chunk columns) an autotuner may pick instead of

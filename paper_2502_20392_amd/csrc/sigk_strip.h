@@ -63,11 +63,36 @@ __device__ __forceinline__ int ring_slot(int col) {
     return ring_slot_of<ring_cols(P)>(col);
 }
 
+// Byte offset of a lane's slot in a ring of ARB columns, stepped one column
+// at a time (two or three vector instructions instead of a division).
+template <int ARB>
+struct RingPos {
+    unsigned b;
+    __device__ __forceinline__ void set(int col) { b = (unsigned)ring_slot_of<ARB>(col) * 8u; }
+    __device__ __forceinline__ void next() {
+        if constexpr ((ARB & (ARB - 1)) == 0)
+            b = (b + 8u) & (unsigned)((ARB - 1) * 8);
+        else
+            b = b + 8u == (unsigned)(ARB * 8) ? 0u : b + 8u;
+    }
+    __device__ __forceinline__ void prev() {
+        if constexpr ((ARB & (ARB - 1)) == 0)
+            b = (b - 8u) & (unsigned)((ARB - 1) * 8);
+        else
+            b = b == 0u ? (unsigned)((ARB - 1) * 8) : b - 8u;
+    }
+};
+
 // D > 0: the channel bucket (d <= D, increments in LDS and registers);
 // D = 0: the cell coefficients come from a field computed beforehand.
-template <int P, int D, int CH, int RB>
+// XC: columns per increment load, the whole chunk where the ring holds it, else 32.
+template <int CH, int RB>
+constexpr int inc_chunk = RB >= CH + kWave - 1 ? CH : 32;
+
+template <int P, int D, int CH, int RB, int TC = CH>
 struct LdsStrip {
-    static_assert(RB >= CH + kWave - 1,
+    static_assert(RB >= inc_chunk<CH, RB> + kWave - 1 && CH % inc_chunk<CH, RB> == 0 &&
+                      CH % TC == 0,
                   "the ring must hold the columns a chunk's steps touch");
     // D > 0: increments of x, [channel][ring slot]; D = 0: the chunk's cell
     // coefficients, [step][lane] (no LDS beyond what D > 0 needs: every byte
@@ -75,7 +100,7 @@ struct LdsStrip {
     // (bin first: its rows are then addressed from one register with the
     // instructions' immediate offsets)
     double bin[CH * P];   // bottom edges of the current chunk (lane 0)
-    double tout[CH * P];  // top edges of the top lane, current chunk
+    double tout[TC * P];  // top edges of the top lane, TC columns at a time
     double dx[D > 0 ? D * RB : CH * kWave];
     float nrm2[D > 0 ? RB : 1];     // |dx_k|^2 of the same columns, rounded up
 };
@@ -89,7 +114,7 @@ struct Acc {
 // in vector registers (the wave runs alone on its SIMD there anyway), so the
 // hot loop neither rebuilds them nor spills them from scalar registers; for
 // small P the registers buy more occupancy instead.
-template <int P, bool kPinVector = (P >= 10 && P <= 12)>
+template <int P, bool kPinVector = false>
 struct Recip {
     double v[2 * P + 1];
     __device__ __forceinline__ void init() {
@@ -97,7 +122,7 @@ struct Recip {
         for (int k = 0; k <= 2 * P; ++k) {
             v[k] = k == 0 ? 0.0 : 1.0 / (double)k;
             if (kPinVector) asm volatile("" : "+v"(v[k]));
-            else if (P <= 8 && k > 2) asm volatile("" : "+s"(v[k]));
+            else if (P <= 12 && k > 2) asm volatile("" : "+s"(v[k]));
         }
     }
     __device__ __forceinline__ double operator()(int k) const { return v[k]; }
@@ -274,6 +299,12 @@ __device__ __forceinline__ double wave_min(double v) {
     return v;
 }
 
+// Cells of an m x n grid on anti-diagonals 0 .. t-1.
+__device__ __forceinline__ long long cells_before(long long t, long long m, long long n) {
+    auto tri = [](long long x) { return x > 0 ? x * (x + 1) / 2 : 0; };
+    return tri(t) - tri(t - m) - tri(t - n) + tri(t - m - n);
+}
+
 // A value equal in every lane, moved to scalar registers.
 __device__ __forceinline__ double uniform_d(double v) {
     const long long b = __double_as_longlong(v);
@@ -310,11 +341,13 @@ __device__ __forceinline__ void lds_copy(double* dst, const double* src) {
 // square truncation of the tile matrix (the paper's fixed-order tile); BLK:
 // the boundary hooks of block checkpointing (left edges from a line, a bottom
 // line for strip 0, right-edge lines written during the sweep).
-template <int P, int D, int CH, int RB, bool SQ = false, bool BLK = false>
+// TC: columns staged per frontier write.
+template <int P, int D, int CH, int RB, bool SQ = false, bool BLK = false, int TC = CH>
 struct StripCtx {
+    static constexpr int XC = inc_chunk<CH, RB>;
     const FwdArgs& a;
     Geo& g;
-    LdsStrip<P, D, CH, RB>& L;
+    LdsStrip<P, D, CH, RB, TC>& L;
     Acc& acc;
     int s;              // strip index
     int nrows;          // valid rows in this strip (<= 64)
@@ -329,16 +362,16 @@ struct StripCtx {
     double cn;          // cell coefficient of the next step
     double dymax2;      // max_l |dy_l|^2 over the strip
     int q;              // Neumann depth of the current chunk
-    unsigned nvalid;
     Recip<P> R;
     int pair;           // pair index (truncation estimate slot)
-    int tload;          // chunks are loaded for steps below this (m; D = 0: all steps)
     // truncation estimate: sum of |c| (|A_{P-1}| + |B_{P-1}|) over the lane's
     // cells of the current chunk, the wave's total of the chunks done, each
     // relative to the local size of K (wave-uniform), and the binary exponent
     // of |K| where the lane's current chunk started
     double tacc, etot;
     int kexp;
+    bool padded = false;  // kpad is set: K at the end of the strip's bottom row
+    double kpad = 0.0;
     // checkpointing (adjoint support)
     double* ck;         // wave-state checkpoints of this strip or null
     double* ckq;        // Neumann depth per chunk (with ck)
@@ -351,7 +384,7 @@ struct StripCtx {
     double* vl = nullptr;
     int vnext = 0;  // step at which lane 0 reaches the last column of its block column
 
-    __device__ StripCtx(const FwdArgs& a_, Geo& g_, LdsStrip<P, D, CH, RB>& L_, Acc& acc_, int s_)
+    __device__ StripCtx(const FwdArgs& a_, Geo& g_, LdsStrip<P, D, CH, RB, TC>& L_, Acc& acc_, int s_)
         : a(a_), g(g_), L(L_), acc(acc_), s(s_) {}
 
     // One cell's local truncation estimate from its input edges (one FMA per
@@ -387,6 +420,28 @@ struct StripCtx {
         return true;
     }
 
+    // Bottom edges of steps [c0, c0+XC) past the last column: the constant K at
+    // the row's end, as if x stood still there.  Lanes past the end of their
+    // row then keep the K of its end (the truncation estimate scales by it).
+    __device__ void pad_bottom(int c0) {
+        if (!has_below || c0 + XC <= g.m) return;
+        const int lane = lane_id();
+        if (!padded) {
+            const double* r = &L.bin[((g.m - 1) % CH) * P];
+            double t = r[P - 1];
+#pragma unroll
+            for (int i = P - 2; i >= 0; --i) t = fma(t, R(i + 1), r[i]);
+            kpad = uniform_d(t);
+            padded = true;
+            __syncthreads();
+        }
+        for (int e = lane; e < XC * P; e += kWave) {
+            const int col = c0 + e / P;
+            if (col >= g.m) L.bin[(col % CH) * P + e % P] = e % P == 0 ? kpad : 0.0;
+        }
+        __syncthreads();
+    }
+
     // Depth of the chunk from the bound of |c|^2 over its cells.  With
     // checkpoints, the depth is stored for the adjoint together with a flag
     // (+kRoughFlag) where the bound allows |c| > 1/2: there the adjoint keeps
@@ -399,7 +454,7 @@ struct StripCtx {
         for (int n = 1; n < P; ++n) qq = cmax2 > a.tau2[n] ? n : qq;
         q = uniform(qq);
         if (ckq && lane_id() == 0)
-            ckq[c0 / CH] = (double)(q + (cmax2 > kRoughC2 ? kRoughFlag : 0));
+            ckq[c0 / XC] = (double)(q + (cmax2 > kRoughC2 ? kRoughFlag : 0));
     }
 
     // D = 0: the coefficients of steps [c0, c0+CH) from the precomputed field
@@ -427,35 +482,41 @@ struct StripCtx {
         }
         if (c0 < g.m && has_below && !load_frontier(c0, min(CH, g.m - c0))) return false;
         __syncthreads();
+        pad_bottom(c0);
         const double cmax = wave_max(cm);
         set_depth(c0, cmax * cmax);
         return true;
     }
 
-    // Load columns [c0, c0+CH) (increments, their norms, bottom edges) and set
-    // the Neumann depth for steps [c0, c0+CH).
+    // Load columns [c0, c0+XC) (increments, their norms, and at a chunk's start
+    // its bottom edges) and set the Neumann depth for steps [c0, c0+XC).  Columns past the last one are
+    // zero increments: a lane past the end of its row then maps with c = 0
+    // (nothing tallied) and the steps need no per-lane test.  A chunk with no
+    // column of the grid keeps the depth of the one before.
     __device__ bool load_chunk(int c0) {
         if constexpr (D == 0) return load_chunk_field(c0);
         const int lane = lane_id();
-        const int nc = min(CH, g.m - c0);
-        // Issue every load before the first wait: the path points of the
-        // chunk's columns (lane j: column c0 + j, clamped to the chunk), then
-        // the frontier columns once the strip below has published them.
-        const int col = c0 + min(lane, nc - 1);
-        const double* xp = g.x + (int64_t)col * a.d;
+        const int nc = min(XC, g.m - c0);
+        const int col = c0 + lane;
         double lo[D > 0 ? D : 1], hi[D > 0 ? D : 1];
+        if (nc > 0) {
+            // Issue every load before the first wait: the path points of the
+            // chunk's columns (lane j: column c0 + j, clamped to the chunk), then
+            // the frontier columns once the strip below has published them.
+            const double* xp = g.x + (int64_t)(c0 + min(lane, nc - 1)) * a.d;
 #pragma unroll
-        for (int ch = 0; ch < D; ++ch) {
-            const int cc = ch < a.d ? ch : 0;
-            lo[ch] = xp[cc];
-            hi[ch] = xp[a.d + cc];
+            for (int ch = 0; ch < D; ++ch) {
+                const int cc = ch < a.d ? ch : 0;
+                lo[ch] = xp[cc];
+                hi[ch] = xp[a.d + cc];
+            }
+            if (has_below && c0 % CH == 0 && !load_frontier(c0, min(CH, g.m - c0))) return false;
         }
-        if (has_below && !load_frontier(c0, nc)) return false;
-        if (lane < nc) {
+        if (lane < XC) {
             double n2 = 0.0;
 #pragma unroll
             for (int ch = 0; ch < D; ++ch) {
-                const double v = ch < a.d ? hi[ch] - lo[ch] : 0.0;
+                const double v = ch < a.d && lane < nc ? hi[ch] - lo[ch] : 0.0;
                 L.dx[ch * RB + ring_slot_of<RB>(col)] = v;
                 n2 = fma(v, v, n2);
             }
@@ -465,7 +526,9 @@ struct StripCtx {
                 (float)fmax(n2 * (1.0 + 1e-6), n2 > 0.0 ? 1.2e-38 : 0.0);
         }
         __syncthreads();
-        // columns touched by steps [c0, c0+CH): [c0-63, c0+nc)
+        pad_bottom(c0);
+        if (nc <= 0) return true;
+        // columns touched by steps [c0, c0+XC): [c0-63, c0+nc)
         double w = 0.0;
         const int k1 = c0 - (kWave - 1) + lane, k2 = c0 + lane;
         if (k1 >= 0 && k1 < c0 + nc) w = (double)L.nrm2[ring_slot_of<RB>(k1)];
@@ -478,7 +541,7 @@ struct StripCtx {
     // to the frontier with coalesced device-coherent stores and publish.
     __device__ void flush(int c0, int c1) {
         double* dst = Fout + (int64_t)c0 * P;
-        const int base = (c0 % CH) * P;
+        const int base = (c0 % TC) * P;
         for (int e = lane_id(); e < (c1 - c0) * P; e += kWave) store_coherent(&dst[e], L.tout[base + e]);
         publish_coherent(&prog[s], c1);
     }
@@ -526,31 +589,39 @@ struct StripCtx {
     // any t; where step t starts a new chunk the value read ahead is stale and
     // is recomputed after load_chunk().
     static constexpr bool kAhead = P <= 8;
+    RingPos<RB> rp;  // (not kAhead) the slot of the step's column, stepped
     __device__ __forceinline__ void prefetch(int t) {
         if constexpr (D == 0) {
             cn = L.dx[((unsigned)t % (unsigned)CH) * kWave + lane_id()];
             return;
         }
-        const int ri = ring_slot_of<RB>(t - lane_id());
+        if constexpr (kAhead) rp.set(t - lane_id());
+        const char* base = (const char*)L.dx + rp.b;
         double c0 = 0.0, c1 = 0.0;
 #pragma unroll
         for (int ch = 0; ch < D; ch += 2) {
-            c0 = fma(dy[ch], L.dx[ch * RB + ri], c0);
-            c1 = fma(dy[ch + 1], L.dx[(ch + 1) * RB + ri], c1);
+            c0 = fma(dy[ch], *(const double*)(base + (size_t)ch * RB * 8), c0);
+            c1 = fma(dy[ch + 1], *(const double*)(base + (size_t)(ch + 1) * RB * 8), c1);
         }
         cn = c0 + c1;
+        if constexpr (!kAhead) rp.next();
     }
 
-    // One step: every lane advances one cell along its row.  QC >= 0 fixes the
-    // Neumann depth at compile time (QC == q), QC < 0 reads q.
-    template <bool EDGE, int QC>
-    __device__ __forceinline__ void step(int t, bool act) {
+    // One step at Neumann depth QC: every lane advances one cell along its row.
+    // The ramps at either end of a strip run the same code: before its row's
+    // first column a lane maps the axis edges (1, 0, ..) with c = 0 onto
+    // themselves (zero increments in the ring) or keeps the left line's edge,
+    // and past its last column it maps with c = 0; neither reaches a cell of
+    // the grid.  (A separate ramp loop with a branch per Neumann term cost
+    // short pairs 6-11%: 33 x 27 points at order 12 took 62.5 us against 56.2,
+    // eight paths of 128 points at order 10 227 us against 214.)  stage: the top lane's edge is staged (t >= 63).
+    template <int QC>
+    __device__ __forceinline__ void step(int t, bool stage) {
         const int lane = lane_id();
-        const int col = t - lane;
         double A[P];
         const double* bsrc = &L.bin[((unsigned)t % (unsigned)CH) * P];  // t >= 0
-        if constexpr (!EDGE && QC >= 0 && P <= 12) {
-            // steady state, depth known at compile time: B-only work first
+        if constexpr (P <= 12) {
+            // the map in two halves: B-only work first
             double bv[P];
             lds_copy<P>(bv, bsrc);
             double c;
@@ -605,120 +676,74 @@ struct StripCtx {
                 B[i] = Bn[i];
                 Ac[i] = An[i];
             }
-            if constexpr (BLK) vline_hook(t, col, act);
-            if (has_above && lane == kWave - 1 && act) {
-                // the top lane's column t - 63, a uniform address
-                const unsigned tc = (unsigned)(t - (kWave - 1));
-                double* dst = &L.tout[(tc % (unsigned)CH) * P];
-                lds_copy<P>(dst, An);
-            }
-            return;
-        }
-#pragma unroll
-        for (int i = 0; i < P; ++i) A[i] = shift_up(Ac[i], bsrc[i]);
-        if (EDGE && col == 0) {
-            bool axis = true;
-            if constexpr (BLK) {
-                if (left != nullptr && lane_ok) {
-                    const double* lp = left + ((int64_t)s * kWave + lane) * P;
-#pragma unroll
-                    for (int i = 0; i < P; ++i) B[i] = lp[i];
-                    axis = false;
-                }
-            }
-            if (axis) {
-#pragma unroll
-                for (int i = 0; i < P; ++i) B[i] = i == 0 ? 1.0 : 0.0;
-            }
-        }
-        // small orders: coefficient computed one step ahead; large orders
-        // (one wave per SIMD, registers scarce): computed here
-        double c;
-        if constexpr (kAhead) {
-            c = cn;
-            prefetch(t + 1);
         } else {
+            // (one wave per SIMD, registers scarce: coefficient computed here)
+#pragma unroll
+            for (int i = 0; i < P; ++i) A[i] = shift_up(Ac[i], bsrc[i]);
             prefetch(t);
-            c = cn;
-        }
-        // at the ramps, lanes outside the grid hold stale values: skip them
-        if (!EDGE || act) {
+            const double c = cn;
             tally(c, A);
             tally(c, B);
-        }
-        double An[P], Bn[P];
-        cell_map<P, SQ>(A, B, c, An, Bn, QC >= 0 ? QC : q, R);
+            double An[P], Bn[P];
+            cell_map<P, SQ>(A, B, c, An, Bn, QC, R);
 #pragma unroll
-        for (int i = 0; i < P; ++i) {
-            B[i] = Bn[i];
-            Ac[i] = An[i];
+            for (int i = 0; i < P; ++i) {
+                B[i] = Bn[i];
+                Ac[i] = An[i];
+            }
         }
-        if constexpr (BLK) vline_hook(t, col, act);
-        if (has_above && lane == kWave - 1 && act) {
-            double* dst = &L.tout[((unsigned)col % (unsigned)CH) * P];
-#pragma unroll
-            for (int i = 0; i < P; ++i) dst[i] = An[i];
+        if constexpr (BLK) vline_hook(t, t - lane, lane_ok && t >= lane);
+        if (stage && lane == kWave - 1) {
+            // the top lane's column t - 63, a uniform address
+            const unsigned tc = (unsigned)(t - (kWave - 1));
+            lds_copy<P>(&L.tout[(tc % (unsigned)TC) * P], Ac);
         }
     }
 
-    // Steady-state steps [t, te) at the chunk's depth q.  For small orders the
-    // depth is dispatched to a loop specialised for it (no branch per term).
+    // Steps [t, te) at the chunk's depth q, dispatched to a loop specialised
+    // for it (no branch per term).
     template <int QD>
-    __device__ __forceinline__ void run_depth(int& t, int te) {
+    __device__ __forceinline__ void run_depth(int& t, int te, bool stage) {
         if constexpr (QD < P - 1) {
             if (q > QD) {
-                run_depth<QD + 1>(t, te);
+                run_depth<QD + 1>(t, te, stage);
                 return;
             }
         }
-        constexpr int QC = QD;
         for (; t < te; ++t) {
             if (ck && ((unsigned)t % (unsigned)ck_every) == 0) save_state(t);
-            step<false, QC>(t, lane_ok);
+            step<QD>(t, stage);
         }
     }
 
-    template <bool EDGE>
-    __device__ bool run(int t0, int t1) {
-        const int lane = lane_id();
+    // Steps 0 .. T-1 of the strip.
+    __device__ bool run(int T) {
         const int m = g.m;
-        int t = t0;
-        while (t < t1) {
-            if ((t % CH) == 0 && t < tload) {
+        int t = 0;
+        while (t < T) {
+            if ((t % XC) == 0) {
                 fold();
                 if (!load_chunk(t)) return false;
+                if constexpr (!kAhead && D > 0) rp.set(t - lane_id());
                 if (kAhead) prefetch(t);
             }
-            // steps up to the next chunk boundary, flush point or range end
-            int te = min(t1, t - (t % CH) + CH);
+            // steps up to the next load, flush point or the end
+            int te = min(T, t - (t % XC) + XC);
+            const bool stage = has_above && t >= kWave - 1;
             if (has_above) {
                 // the top lane finishes column tc at step tc + 63
                 const int tc = t - (kWave - 1);
-                const int nxt = tc < 0 ? CH - 1 : tc - (tc % CH) + CH - 1;
-                te = min(te, min(nxt, m - 1) + kWave);
+                const int nxt = tc - (tc % TC) + TC - 1;
+                te = min(te, stage ? min(nxt, m - 1) + kWave : kWave - 1);
             }
-            if (ck) te = min(te, t - (t % ck_every) + ck_every);
-            const long long fl = cell_flops(P, q, D > 0 ? a.d : 0);  // D = 0: counted by the field
-            if (EDGE) {
-                for (; t < te; ++t) {
-                    if (ck && ((unsigned)t % (unsigned)ck_every) == 0) save_state(t);
-                    const int col = t - lane;
-                    const bool act = lane_ok && col >= 0 && col < m;
-                    const unsigned cnt = (unsigned)__builtin_popcountll(ballot(act));
-                    acc.cells += cnt;
-                    acc.flops += (unsigned long long)cnt * (unsigned long long)fl;
-                    step<true, -1>(t, act);
-                }
-            } else {
-                const int n = te - t;
-                acc.cells += (unsigned long long)n * nvalid;
-                acc.flops += (unsigned long long)n * nvalid * (unsigned long long)fl;
-                run_depth<0>(t, te);
-            }
-            if (has_above) {
+            te = uniform(te);
+            const long long cnt = cells_before(te, m, nrows) - cells_before(t, m, nrows);
+            acc.cells += (unsigned long long)cnt;
+            acc.flops += (unsigned long long)(cnt * cell_flops(P, q, D > 0 ? a.d : 0));
+            run_depth<0>(t, te, stage);  // (D = 0: <dx, dy> is counted by the field)
+            if (stage) {
                 const int tc = t - 1 - (kWave - 1);
-                if (tc >= 0 && tc < m && ((tc % CH) == CH - 1 || tc == m - 1))
-                    flush(tc - tc % CH, tc + 1);
+                if ((tc % TC) == TC - 1 || tc == m - 1) flush(tc - tc % TC, tc + 1);
             }
         }
         return true;
@@ -733,7 +758,6 @@ struct StripCtx {
         lane_ok = lane < nrows;
         has_below = s > 0 || (BLK && below_line);
         has_above = row0 + kWave < g.n;
-        nvalid = (unsigned)nrows;
         if constexpr (BLK) {
             vnext = a.blk.cb - 1;
         }
@@ -748,7 +772,6 @@ struct StripCtx {
             n2 = fma(dy[ch], dy[ch], n2);
         }
         dymax2 = wave_max(n2);
-        tload = D == 0 ? m + nrows - 1 : m;
         q = P - 1;
         tacc = 0.0;
         etot = 0.0;
@@ -758,16 +781,29 @@ struct StripCtx {
             B[i] = i == 0 ? 1.0 : 0.0;
             Ac[i] = B[i];
         }
+        if constexpr (BLK) {
+            // left edges on a left line (held until the lane reaches column 0)
+            if (left != nullptr && lane_ok) {
+                const double* lp = left + ((int64_t)s * kWave + lane) * P;
+#pragma unroll
+                for (int i = 0; i < P; ++i) B[i] = lp[i];
+            }
+        }
         if (!has_below) {
             // bottom row of the grid: K = 1 on the axis t = 0
-                for (int e = lane; e < CH * P; e += kWave) L.bin[e] = (e % P) == 0 ? 1.0 : 0.0;
-            __syncthreads();
+            for (int e = lane; e < CH * P; e += kWave) L.bin[e] = (e % P) == 0 ? 1.0 : 0.0;
         }
+        if constexpr (D > 0) {
+            // zero increments in the 63 columns before the first
+            if (lane < kWave - 1) {
+                const int sl = ring_slot_of<RB>(lane - (kWave - 1));
+#pragma unroll
+                for (int ch = 0; ch < D; ++ch) L.dx[ch * RB + sl] = 0.0;
+            }
+        }
+        __syncthreads();
         const int T = m + nrows - 1;
-        const int tA = min(T, kWave);
-        if (!run<true>(0, tA)) return false;
-        if (m > kWave && !run<false>(kWave, m)) return false;
-        if (!run<true>(max(tA, m), T)) return false;
+        if (!run(T)) return false;
         if (ck && (T % ck_every) == 0) save_state(T);
         // the strip's share of the pair's truncation estimate
         fold();
