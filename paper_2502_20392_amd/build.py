@@ -26,7 +26,8 @@ EXTRA = os.environ.get("SIGK_EXTRA_FLAGS", "").split()
 FLAGS = EXTRA + ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}", "-munsafe-fp-atomics",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wall", "-Wno-unused-function", "-Wno-unused-variable", "-I", INCLUDE]
-HEADERS = ["sigk_internal.h", "sigk_device.h", "sigk_strip.h", "sigk_adjoint.h"]
+HEADERS = ["sigk_internal.h", "sigk_device.h", "sigk_strip.h", "sigk_adjoint.h",
+           "sigk_team.h"]
 
 
 def _variants(name):

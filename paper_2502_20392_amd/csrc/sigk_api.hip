@@ -52,6 +52,15 @@ const Variant kFwdSqTable[] = {SIGK_FWDSQ_VARIANTS(SIGK_V_FWDSQ)};
 const Variant kFwdGTable[] = {SIGK_FWDG_VARIANTS(SIGK_V_FWDG)};
 #undef SIGK_V_FWDG
 
+struct TeamVariant {
+    int P, D;
+    hipError_t (*launch)(const FwdArgs&, int, hipStream_t);
+    int (*occ)(int);
+};
+#define SIGK_V_TEAM(P, D) {P, D, launch_team_##P##_##D, occupancy_team_##P##_##D},
+const TeamVariant kTeamTable[] = {SIGK_FWD_VARIANTS(SIGK_V_TEAM) SIGK_FWDG_VARIANTS(SIGK_V_TEAM)};
+#undef SIGK_V_TEAM
+
 int round_order(int order) {
     if (order <= 0) order = 12;
     for (int p : kOrders)
@@ -101,6 +110,11 @@ const Variant* find_fwd(int P, int D, uint32_t flags = 0, int tile = 0) {
         if (v.P == P && v.D == D) return &v;
     return nullptr;
 }
+const TeamVariant* find_team(int P, int D) {
+    for (const TeamVariant& v : kTeamTable)
+        if (v.P == P && v.D == D) return &v;
+    return nullptr;
+}
 const Variant* find_bwd(int P, int D, uint32_t flags = 0) {
     if (flags & SIGK_FLAG_SQUARE) return nullptr;  // forward-only mode
     for (const Variant& v : kBwdTable)
@@ -124,12 +138,20 @@ enum {
     kKernelCkpt = 2,
     kKernelFwdSq = 3,
     kKernelLines = 4,
-    kKernelFwdT = 5  // forward with the alternative work tile
+    kKernelFwdT = 5,  // forward with the alternative work tile
+    kKernelTeam = 16  // + compute waves per team
 };
 
 int fwd_kind(int P, int D, uint32_t flags, int tile) {
     return (flags & SIGK_FLAG_SQUARE) ? kKernelFwdSq
                                       : (alt_tile(P, D, tile) ? kKernelFwdT : kKernelFwd);
+}
+
+int device_cus() {
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev >= 64) return 256;
+    std::lock_guard<std::mutex> lk(g_mu);
+    return g_cus[dev] > 0 ? g_cus[dev] : 256;
 }
 
 int device_wgs(int P, int D, int kind) {
@@ -144,7 +166,10 @@ int device_wgs(int P, int D, int kind) {
         g_cus[dev] = cus;
     }
     int occ = 0;
-    if (kind == kKernelFwd || kind == kKernelFwdSq || kind == kKernelFwdT) {
+    if (kind >= kKernelTeam) {
+        const TeamVariant* v = find_team(P, D);
+        occ = v ? v->occ(kind - kKernelTeam) : 0;
+    } else if (kind == kKernelFwd || kind == kKernelFwdSq || kind == kKernelFwdT) {
         const Variant* v = find_fwd(P, D, kind == kKernelFwdSq ? SIGK_FLAG_SQUARE : 0,
                                     kind == kKernelFwdT ? alt_chunk_cols(P, D) : 0);
         occ = v ? v->occ_fwd() : 0;
@@ -159,6 +184,43 @@ int device_wgs(int P, int D, int kind) {
     int value = occ * (dev < 64 ? g_cus[dev] : 256);
     g_occ.push_back({dev, P, D, kind, value});
     return value;
+}
+
+// Compute waves per team of a Gram call's forward sweep (the team kernel), 0
+// for the one-wave kernel.  The team kernel shortens the dependency chain of a
+// pair (a start lag of 64 + team_sub steps per strip against 63 + chunk) but
+// runs fewer compute waves, so it is taken where the launch's time is that
+// chain: both kernels' times in steps are estimated as the larger of the chain
+// and of the work over the resident waves.  Measured one-wave over team at
+// lengths 100-2000, orders 5-16 and 1-2048 pairs: 1.05-1.49 where this rule
+// takes the team (order 10, length 1000, d 3: 1.38 for 1 pair, 1.34 for 64),
+// 0.4-1.1 where it does not (0.80 for 512).  An explicit grid or tile width
+// asks for the one-wave kernel.
+int team_waves(int P, int D, const sigk_opts& op, int64_t strips, int64_t npairs, int64_t m) {
+    if (strips < 2 || op.grid > 0 || op.tile_cols != 0 || (op.flags & SIGK_FLAG_SQUARE)) return 0;
+    const TeamVariant* v = find_team(P, D);
+    if (!v) return 0;
+    const int64_t wmax = v->occ(-1);
+    const int64_t groups = (strips + wmax - 1) / wmax;
+    const int W = (int)((strips + groups - 1) / groups);
+    const int lag = kWave + team_steps(P);
+    const double sweep = (double)(m + kWave - 1), simds = 4.0 * device_cus();
+    // a step of one of w waves on a SIMD against a lone wave's (5.25, 7.1 and
+    // 9.1 cycles per FP64 instruction measured for 1, 2 and 3)
+    auto slow = [](double w) { return 1.0 + 0.37 * std::max(0.0, w - 1.0); };
+    const double cap1 = device_wgs(P, D, kKernelFwd), all1 = (double)(npairs * strips);
+    const double cap_t = device_wgs(P, D, kKernelTeam + W), all_t = (double)(npairs * groups);
+    const double f1 = slow(std::min(all1, cap1) / simds);
+    const double f_t = slow(std::min(all_t, cap_t) * (W + 1) / simds);
+    // the one-wave kernel's chunk round trips, against its steps
+    const double trips = P <= 8 ? 1.15 : P <= 12 ? 1.1 : 1.03;
+    const double chain1 =
+        trips * (sweep + (double)(strips - 1) * (fwd_chunk_cols(P, D) + kWave - 1));
+    const double chain_t = sweep + (double)(strips - 1) * lag;
+    const double t1 = std::max(chain1 * (all1 <= cap1 ? f1 : 1.0), sweep * all1 / cap1 * f1);
+    const double t_t = std::max(chain_t * (all_t <= cap_t ? f_t : 1.0),
+                                std::ceil(all_t / cap_t) * (sweep + 0.5 * (W - 1) * lag) * f_t);
+    return t_t < 0.95 * t1 ? W : 0;
 }
 
 // Per-cell Neumann tolerance.  A dropped term n is bounded by |c|^n/(n!)^2
@@ -550,9 +612,18 @@ int sigk_gram(const double* X, int64_t nx, const double* Y, int64_t ny, int64_t 
         e = launch_delta_gemm(a, s);
         if (e != hipSuccess) return device_error(e);
     }
-    int grid = op.grid > 0 ? op.grid : device_wgs(P, D, fwd_kind(P, D, op.flags, op.tile_cols));
-    grid = (int)std::min<int64_t>(grid, a.ntickets);
-    e = v->fwd(a, std::max(grid, 1), s);
+    const int team = team_waves(P, D, op, L.strips, L.npairs, lx - 1);
+    if (team > 0) {
+        a.team = team;
+        a.ntickets = L.npairs * ((L.strips + team - 1) / team);
+        const int grid = (int)std::min<int64_t>(device_wgs(P, D, kKernelTeam + team), a.ntickets);
+        e = find_team(P, D)->launch(a, std::max(grid, 1), s);
+    } else {
+        int grid =
+            op.grid > 0 ? op.grid : device_wgs(P, D, fwd_kind(P, D, op.flags, op.tile_cols));
+        grid = (int)std::min<int64_t>(grid, a.ntickets);
+        e = v->fwd(a, std::max(grid, 1), s);
+    }
     if (e == hipSuccess) e = launch_finalize(hdr, est, L.npairs, budget_of(op), s);
     if (e != hipSuccess) return device_error(e);
     return SIGK_OK;

@@ -14,6 +14,7 @@
 // other frontier chunk width (alt_chunk_cols) as launch_fwdt_P_D /
 // occupancy_fwdt_P_D.
 #include "sigk_strip.h"
+#include "sigk_team.h"
 
 #ifndef SIGK_P
 #define SIGK_P 8
@@ -102,5 +103,29 @@ int SIGK_NAME(SIGK_OCC, SIGK_P, SIGK_D)() {
         return 0;
     return nb;
 }
+
+#if !SIGK_SQ && !SIGK_ALT
+hipError_t SIGK_NAME(launch_team_, SIGK_P, SIGK_D)(const FwdArgs& a, int grid, hipStream_t s) {
+    const size_t lds = team_lds_bytes<SIGK_P, SIGK_D>(a.team);
+    hipError_t e = hipFuncSetAttribute((const void*)team_kernel<SIGK_P, SIGK_D>,
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((team_kernel<SIGK_P, SIGK_D>), dim3(grid), dim3(kWave * (a.team + 1)),
+                       lds, s, a);
+    return hipGetLastError();
+}
+
+int SIGK_NAME(occupancy_team_, SIGK_P, SIGK_D)(int waves) {
+    if (waves < 0) return team_max_waves<SIGK_P, SIGK_D>;
+    int nb = 0;
+    const size_t lds = team_lds_bytes<SIGK_P, SIGK_D>(waves);
+    if (hipFuncSetAttribute((const void*)team_kernel<SIGK_P, SIGK_D>,
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, team_kernel<SIGK_P, SIGK_D>,
+                                                     kWave * (waves + 1), lds) != hipSuccess)
+        return 0;
+    return nb;
+}
+#endif
 
 }  // namespace sigk

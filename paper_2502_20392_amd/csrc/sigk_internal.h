@@ -60,6 +60,8 @@ __host__ __device__ constexpr int ring_cols(int P) { return P <= 8 ? 128 : 96; }
 __host__ __device__ constexpr int fwd_ring_cols(int P, int D) {
     return fwd_chunk_cols(P, D) == 64 ? 128 : ring_cols(P);
 }
+// Steps between two tests of a team's counters (sigk_team.h).
+__host__ __device__ constexpr int team_steps(int P) { return P <= 8 ? 16 : 8; }
 // Columns of the ring in the plain and the checkpointing sweep of a variant
 // with 64-column chunks: orders 10-12 with 8 < d <= 16 load increments (and
 // set the Neumann depth) 32 columns at a time, so that two waves per SIMD fit
@@ -173,6 +175,7 @@ struct FwdArgs {
     int symmetric;
     int d;
     int strips;        // strips per pair (gram mode)
+    int team;          // compute waves per workgroup (team kernel)
     const double* X;   // gram: X batch; table: pool
     const double* Y;   // gram: Y batch; table: pool
     int64_t nx, ny, lx, ly;
@@ -231,6 +234,14 @@ SIGK_FWD_VARIANTS(SIGK_DECL_FWDT)
     int occupancy_fwdsq_##P##_##D();
 SIGK_FWDSQ_VARIANTS(SIGK_DECL_FWDSQ)
 #undef SIGK_DECL_FWDSQ
+
+// The team kernels (gram mode, FwdArgs::team compute waves per workgroup).
+#define SIGK_DECL_TEAM(P, D) \
+    hipError_t launch_team_##P##_##D(const FwdArgs& a, int grid, hipStream_t s); \
+    int occupancy_team_##P##_##D(int waves);
+SIGK_FWD_VARIANTS(SIGK_DECL_TEAM)
+SIGK_FWDG_VARIANTS(SIGK_DECL_TEAM)
+#undef SIGK_DECL_TEAM
 
 // The cell-coefficient field of every pair of a Gram call (FwdArgs in gram
 // mode with delta set), on the matrix cores.

@@ -43,3 +43,41 @@ def test_one_wave_edges(dev, order, d):
     for shape in SHAPES:
         for tile in sk().api.tile_options(order, d):
             check(dev, order, d, shape, grid=3, tile=tile)
+
+
+@pytest.mark.parametrize("order,d", [(4, 2), (5, 8), (6, 3), (8, 16), (10, 3), (10, 16), (12, 3),
+                                     (12, 32), (16, 16), (20, 3), (24, 8), (6, 40), (12, 40),
+                                     (20, 33)])
+def test_team_edges(dev, order, d):
+    """Teams of waves (the default for a pair of two strips or more): strips that
+    are not a whole team, a last strip of one row, paths shorter than a block of
+    steps, several teams in a chain, several pairs.  The same cell maps as the
+    one-wave kernel, at Neumann depths chosen over other chunks: equal to a few
+    roundings, and both within the parity bound of the oracle."""
+    import oracle
+    n = 3
+    for lx, ly in ((2, 66), (9, 130), (33, 129), (64, 194), (65, 258), (100, 322), (200, 385),
+                   (17, 705)):
+        X = synth.brownian(n, lx, d, 0.05 if order == 4 else 0.4 / np.sqrt(d), seed=order + lx)
+        Y = synth.brownian(2, ly, d, 0.05 if order == 4 else 0.4 / np.sqrt(d), seed=order + ly)
+        G = sk().gram(T(X, dev), T(Y, dev), order=order).cpu().numpy()
+        c = sk().counters()
+        assert not c["status"] & ~1 and c["cells"] == 2 * n * (lx - 1) * (ly - 1), (lx, ly, c)
+        G1 = sk().gram(T(X, dev), T(Y, dev), order=order, grid=5).cpu().numpy()
+        assert sk().counters()["status"] == c["status"], (lx, ly)
+        assert np.max(np.abs(G - G1) / np.maximum(np.abs(G1), 1.0)) < 1e-12, (lx, ly)
+        if c["status"] & 1:  # the order is too small for this pair: no parity promised
+            continue
+        ref = np.array([[oracle.pair(x, y) for y in Y] for x in X])
+        assert np.max(np.abs(G - ref) / np.maximum(np.abs(ref), 1.0)) < 1e-10, (lx, ly)
+
+
+def test_team_nonfinite(dev):
+    """A non-finite point anywhere in a pair of several strips still raises the status."""
+    X = synth.brownian(1, 150, 3, 0.5, seed=1)[0]
+    Y = synth.brownian(1, 300, 3, 0.5, seed=2)[0]
+    for which, row in (("x", 0), ("x", 149), ("y", 5), ("y", 299)):
+        x, y = X.copy(), Y.copy()
+        (x if which == "x" else y)[row, 1] = np.nan
+        k = sk().pair(T(x, dev), T(y, dev), order=8).item()
+        assert not np.isfinite(k) and sk().counters()["status"] & 2, (which, row)
