@@ -214,7 +214,7 @@ __device__ __forceinline__ Geo resolve_block(const FwdArgs& a, int slot, int P, 
     g.ckpt = (int64_t)slot * k.slot_ckpt;
     g.delta = 0;
     g.prog = slot * k.slot_prog + 1;
-    g.o1 = -1;
+    g.o1 = 0;  // (written only where the launch has an output: a single block)
     g.o2 = -1;
     r.I = I;
     r.J = J;
