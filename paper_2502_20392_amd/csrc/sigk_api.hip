@@ -267,6 +267,7 @@ __global__ void reset_kernel(WsHeader* h, int* prog, int64_t nprog, double* out,
         h->cells = 0;
         h->flops = 0;
         h->order = order;
+        h->done = 0;
         h->trunc_max = 0.0;
         h->bwd_cells = 0;
         h->bwd_flops = 0;
@@ -486,6 +487,8 @@ int fwd_pass(const sigk_plan* plan, const double* pool, double* out, char* base,
     a.progress = (int*)(base + plan->o_prog);
     a.hdr = hdr;
     a.trunc_est = est;
+    a.budget = budget_of(plan->opts);
+    a.check = plan->npairs <= kFusedCheckPairs;
     const Variant* v = find_fwd(plan->P, plan->D, plan->opts.flags, plan->opts.tile_cols);
     if (!v) return SIGK_EUNSUPPORTED;
     int grid = plan->opts.grid > 0
@@ -494,7 +497,8 @@ int fwd_pass(const sigk_plan* plan, const double* pool, double* out, char* base,
                                 fwd_kind(plan->P, plan->D, plan->opts.flags, plan->opts.tile_cols));
     grid = (int)std::min<int64_t>(grid, a.ntickets);
     hipError_t e = v->fwd(a, std::max(grid, 1), s);
-    if (e == hipSuccess) e = launch_finalize(hdr, est, plan->npairs, budget_of(plan->opts), s);
+    if (e == hipSuccess && !a.check)
+        e = launch_finalize(hdr, est, plan->npairs, budget_of(plan->opts), s);
     if (e != hipSuccess) return device_error(e);
     return SIGK_OK;
 }
@@ -583,8 +587,14 @@ int sigk_gram(const double* X, int64_t nx, const double* Y, int64_t ny, int64_t 
     WsHeader* hdr = (WsHeader*)(base + L.hdr);
     int* prog = (int*)(base + L.prog);
     double* est = (double*)(base + L.est);
-    hipError_t e = launch_reset(hdr, prog, L.nprog, G, nx * ny, est, L.npairs, (unsigned)P, s);
-    if (e != hipSuccess) return device_error(e);
+    // (a single strip needs no reset: its wave claims no ticket, waits on no
+    // flag and sets the header and the estimate itself)
+    const bool solo = L.npairs * L.strips == 1 && lx > 1 && D > 0;
+    hipError_t e = hipSuccess;
+    if (!solo) {
+        e = launch_reset(hdr, prog, L.nprog, G, nx * ny, est, L.npairs, (unsigned)P, s);
+        if (e != hipSuccess) return device_error(e);
+    }
     if (lx < 2 || ly < 2) return SIGK_OK;
     FwdArgs a;
     std::memset(&a, 0, sizeof a);
@@ -606,6 +616,9 @@ int sigk_gram(const double* X, int64_t nx, const double* Y, int64_t ny, int64_t 
     a.hdr = hdr;
     a.ckpt = nullptr;
     a.trunc_est = est;
+    a.budget = budget_of(op);
+    a.check = L.npairs <= kFusedCheckPairs;
+    a.solo = solo ? P : 0;
     if (D == 0) {
         a.delta = (double*)(base + L.field);
         a.delta_pair = L.field_pair;
@@ -624,7 +637,8 @@ int sigk_gram(const double* X, int64_t nx, const double* Y, int64_t ny, int64_t 
         grid = (int)std::min<int64_t>(grid, a.ntickets);
         e = v->fwd(a, std::max(grid, 1), s);
     }
-    if (e == hipSuccess) e = launch_finalize(hdr, est, L.npairs, budget_of(op), s);
+    if (e == hipSuccess && !a.check)
+        e = launch_finalize(hdr, est, L.npairs, budget_of(op), s);
     if (e != hipSuccess) return device_error(e);
     return SIGK_OK;
 }

@@ -42,12 +42,14 @@ __global__ void __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(fwd_
     __shared__ LdsStrip<P, D, CH, RB, TC> L;
     Acc acc;
     const int lane = lane_id();
-    for (;;) {
-        unsigned t = 0;
-        if (lane == 0) t = atomicAdd(&a.hdr->ticket, 1u);
-        t = (unsigned)uniform((int)t);
+    for (unsigned round = 0;; ++round) {
+        unsigned t = round;
+        if (!a.solo) {
+            if (lane == 0) t = atomicAdd(&a.hdr->ticket, 1u);
+            t = (unsigned)uniform((int)t);
+        }
         if ((int64_t)t >= a.ntickets) break;
-        if (uniform((int)(load_status(a.hdr) & SIGK_ERR_WATCHDOG))) break;
+        if (!a.solo && uniform((int)(load_status(a.hdr) & SIGK_ERR_WATCHDOG))) break;
         int pair, strip;
         if (a.mode == kModeGram) {
             pair = (int)((int64_t)t % a.npairs);
@@ -68,11 +70,7 @@ __global__ void __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(fwd_
         S.ck_every = 1;
         if (!S.sweep()) break;
     }
-    if (lane == 0) {
-        atomicAdd(&a.hdr->cells, acc.cells);
-        atomicAdd(&a.hdr->flops, acc.flops);
-        if (acc.status) atomicOr(&a.hdr->status, acc.status);
-    }
+    finish_forward(a, acc, true);
 }
 
 #define SIGK_CAT3(a, b, c) a##b##_##c

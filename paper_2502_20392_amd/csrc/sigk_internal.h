@@ -86,6 +86,10 @@ __host__ __device__ constexpr int alt_chunk_cols(int P, int D) {
     return fwd_chunk_cols(P, D) == 64 ? 32 : 64;
 }
 
+// Pairs up to which the forward launch's last workgroup checks the truncation
+// estimates itself (beyond, a kernel of its own has more threads for it).
+constexpr int64_t kFusedCheckPairs = 4096;
+
 // Per-pair geometry for table mode (ragged batches).  Offsets in elements.
 struct PairDesc {
     int64_t x_off;      // first double of path x in the pool
@@ -135,7 +139,8 @@ struct WsHeader {
     unsigned long long bwd_cells;  // cells of the adjoint sweep
     unsigned long long bwd_flops;  // algorithmic flops of the adjoint sweep
                                    // (adjoint maps + recomputed forward maps)
-    unsigned pad[50];
+    unsigned done;     // workgroups that have finished the forward sweep
+    unsigned pad[49];
 };
 static_assert(sizeof(WsHeader) == 256, "header size");
 
@@ -191,6 +196,9 @@ struct FwdArgs {
     double tau2[kMaxP];  // Neumann term n is needed where |c|^2 > tau2[n]
                          // (|c|^n/(n!)^2 > tol); all < 0 for the fixed depth
     double* trunc_est;   // [npairs] truncation estimate per pair (strips add)
+    double budget;       // of a pair's truncation estimate (fused check)
+    int check;           // the last workgroup checks the estimates
+    int solo;            // one strip in all: its wave also sets the header
     double* delta;       // channel bucket 0: cell coefficients, per pair
                          // [strips][delta_steps(m)][64] (gram mode)
     int64_t delta_pair;  // doubles per pair in delta

@@ -305,6 +305,72 @@ __device__ __forceinline__ long long cells_before(long long t, long long m, long
     return tri(t) - tri(t - m) - tri(t - n) + tri(t - m - n);
 }
 
+// End of a forward launch, by one wave of each workgroup: add its counters to
+// the header; the last workgroup to arrive compares every pair's truncation
+// estimate with the budget.  (Two launches less around short calls: the check
+// and, for a single strip, the reset.  33 x 27 points at order 12: 56 us with
+// them, 50 without.)  Estimates are summed by device-scope atomics, which
+// have completed before the arrival is counted, and read coherently.
+__device__ __forceinline__ void finish_forward(const FwdArgs& a, const Acc& acc, bool mine) {
+    const int lane = lane_id();
+    WsHeader* h = a.hdr;
+    if (a.solo) {
+        if (!mine || lane != 0) return;
+        const double v = a.trunc_est[0];
+        h->status = acc.status | (isfinite(v) ? (v > a.budget ? SIGK_WARN_TRUNC : 0u)
+                                              : SIGK_WARN_NONFINITE);
+        h->ticket = 1;
+        h->cells = acc.cells;
+        h->flops = acc.flops;
+        h->order = (unsigned)a.solo;
+        h->ticket2 = 0;
+        h->trunc_max = isfinite(v) ? fmax(v, 0.0) : 0.0;
+        h->bwd_cells = 0;
+        h->bwd_flops = 0;
+        h->done = 1;
+        return;
+    }
+    if (lane == 0) {
+        atomicAdd(&h->cells, acc.cells);
+        atomicAdd(&h->flops, acc.flops);
+        if (acc.status) atomicOr(&h->status, acc.status);
+    }
+    if (!a.check) return;
+    // every wave of the workgroup has added its estimates
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    if (!mine) return;
+    unsigned n = 0;
+    if (lane == 0)
+        n = __hip_atomic_fetch_add(&h->done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (uniform((int)n) != (int)gridDim.x - 1) return;
+    double mx = 0.0;
+    unsigned bits = 0;
+    for (int64_t p0 = 0; p0 < a.npairs; p0 += 8 * kWave) {
+        const int64_t left = a.npairs - p0;
+        const CoherentSpan src(a.trunc_est + p0, (int)(left < 8 * kWave ? left : 8 * kWave));
+        double v[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) v[k] = src.load(lane + k * kWave);  // 0 past the end
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            if (!isfinite(v[k])) bits |= SIGK_WARN_NONFINITE;
+            else {
+                if (v[k] > a.budget) bits |= SIGK_WARN_TRUNC;
+                mx = fmax(mx, v[k]);
+            }
+        }
+    }
+    mx = wave_max(mx);
+    const unsigned all = (ballot(bits & SIGK_WARN_TRUNC) ? SIGK_WARN_TRUNC : 0u) |
+                         (ballot(bits & SIGK_WARN_NONFINITE) ? SIGK_WARN_NONFINITE : 0u);
+    if (lane == 0) {
+        h->trunc_max = mx;
+        if (all) atomicOr(&h->status, all);
+    }
+}
+
 // A value equal in every lane, moved to scalar registers.
 __device__ __forceinline__ double uniform_d(double v) {
     const long long b = __double_as_longlong(v);
@@ -809,7 +875,10 @@ struct StripCtx {
         fold();
         const double est = etot * inv_factorial<P>();
         if (!isfinite(est)) acc.status |= SIGK_WARN_NONFINITE;
-        if (lane == 0 && a.trunc_est) atomicAdd(&a.trunc_est[pair], est);
+        if (lane == 0 && a.trunc_est) {
+            if (a.solo) a.trunc_est[0] = est;
+            else atomicAdd(&a.trunc_est[pair], est);
+        }
         if (!has_above) {
             // the last row's lane holds the top edge of the corner cell
             const bool mine = lane == nrows - 1;

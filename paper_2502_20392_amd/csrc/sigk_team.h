@@ -634,11 +634,7 @@ __global__ void __launch_bounds__(kWave*(team_max_waves<P, D> + 1))
             }
         }
     }
-    if (lane == 0 && w < tg.W) {
-        atomicAdd(&a.hdr->cells, acc.cells);
-        atomicAdd(&a.hdr->flops, acc.flops);
-        if (acc.status) atomicOr(&a.hdr->status, acc.status);
-    }
+    finish_forward(a, acc, w == 0);
 }
 
 }  // namespace sigk

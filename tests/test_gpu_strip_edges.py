@@ -81,3 +81,31 @@ def test_team_nonfinite(dev):
         (x if which == "x" else y)[row, 1] = np.nan
         k = sk().pair(T(x, dev), T(y, dev), order=8).item()
         assert not np.isfinite(k) and sk().counters()["status"] & 2, (which, row)
+
+
+@pytest.mark.parametrize("scale", [0.02, 1.0])
+@pytest.mark.parametrize("npairs", [1, 63, 513, 4096, 4100])
+def test_truncation_check_batch_sizes(dev, npairs, scale):
+    """The end-of-launch check over one pair (whose wave sets the header itself),
+    several loads of estimates and more pairs than the launch checks itself: one
+    rough pair among smooth ones counts wherever it stands, and a workspace full
+    of another call's bytes changes nothing.  Expected from the per-pair
+    estimates of a plan."""
+    x = scale * synth.brownian(1, 9, 2, 1.0, seed=5)
+    smooth = synth.brownian(npairs, 9, 2, 0.02, seed=6)
+    off = np.arange(npairs + 2, dtype=np.int64) * 9
+    pairs = np.stack([np.zeros(npairs), 1 + np.arange(npairs)], 1).astype(np.int32)
+    plan = sk().RaggedPlan(off, pairs, 2, order=6, device=dev)
+    for at in sorted({0, npairs // 2, npairs - 1}):
+        Y = smooth.copy()
+        rough = Y.copy()
+        rough[at] *= 200.0
+        ws = torch.full((1 << 22,), 255, dtype=torch.uint8, device=dev)
+        for B in (Y, rough, Y):
+            plan.run(T(np.concatenate([x, B]).reshape(-1, 2), dev))
+            est = plan.estimates().max().item()
+            sk().gram(T(x, dev), T(B, dev), order=6, ws=ws)
+            c = sk().counters(ws)
+            assert c["status"] == int(est > 2.0 ** -36), (at, est, c)
+            assert c["cells"] == 64 * npairs and c["order"] == 6, c
+            assert abs(c["trunc_est"] - est) <= 1e-12 * est, (est, c)
