@@ -32,23 +32,24 @@ struct Variant {
     hipError_t (*bwd)(const BwdArgs&, int, hipStream_t);
     int (*occ_ckpt)();
     int (*occ_bwd)();
+    hipError_t (*bwd_two)(const BwdArgs&, int, hipStream_t);
 };
 
-#define SIGK_V_FWD(P, D) {P, D, launch_fwd_##P##_##D, occupancy_fwd_##P##_##D, nullptr, nullptr, nullptr, nullptr},
+#define SIGK_V_FWD(P, D) {P, D, launch_fwd_##P##_##D, occupancy_fwd_##P##_##D, nullptr, nullptr, nullptr, nullptr, nullptr},
 const Variant kFwdTable[] = {SIGK_FWD_VARIANTS(SIGK_V_FWD)};
 #undef SIGK_V_FWD
 // (the adjoint variants' fwd slot is the first sweep of a long pair's
 // gradient, the lines kernel)
-#define SIGK_V_BWD(P, D) {P, D, launch_lines_##P##_##D, occupancy_lines_##P##_##D, launch_ckpt_##P##_##D, launch_bwd_##P##_##D, occupancy_ckpt_##P##_##D, occupancy_bwd_##P##_##D},
+#define SIGK_V_BWD(P, D) {P, D, launch_lines_##P##_##D, occupancy_lines_##P##_##D, launch_ckpt_##P##_##D, launch_bwd_##P##_##D, occupancy_ckpt_##P##_##D, occupancy_bwd_##P##_##D, launch_bwd_two_##P##_##D},
 const Variant kBwdTable[] = {SIGK_BWD_VARIANTS(SIGK_V_BWD)};
 #undef SIGK_V_BWD
-#define SIGK_V_FWDT(P, D) {P, D, launch_fwdt_##P##_##D, occupancy_fwdt_##P##_##D, nullptr, nullptr, nullptr, nullptr},
+#define SIGK_V_FWDT(P, D) {P, D, launch_fwdt_##P##_##D, occupancy_fwdt_##P##_##D, nullptr, nullptr, nullptr, nullptr, nullptr},
 const Variant kFwdTTable[] = {SIGK_FWD_VARIANTS(SIGK_V_FWDT)};
 #undef SIGK_V_FWDT
-#define SIGK_V_FWDSQ(P, D) {P, D, launch_fwdsq_##P##_##D, occupancy_fwdsq_##P##_##D, nullptr, nullptr, nullptr, nullptr},
+#define SIGK_V_FWDSQ(P, D) {P, D, launch_fwdsq_##P##_##D, occupancy_fwdsq_##P##_##D, nullptr, nullptr, nullptr, nullptr, nullptr},
 const Variant kFwdSqTable[] = {SIGK_FWDSQ_VARIANTS(SIGK_V_FWDSQ)};
 #undef SIGK_V_FWDSQ
-#define SIGK_V_FWDG(P, D) {P, D, launch_fwd_##P##_##D, occupancy_fwd_##P##_##D, nullptr, nullptr, nullptr, nullptr},
+#define SIGK_V_FWDG(P, D) {P, D, launch_fwd_##P##_##D, occupancy_fwd_##P##_##D, nullptr, nullptr, nullptr, nullptr, nullptr},
 const Variant kFwdGTable[] = {SIGK_FWDG_VARIANTS(SIGK_V_FWDG)};
 #undef SIGK_V_FWDG
 
@@ -371,7 +372,7 @@ struct sigk_plan {
     int64_t snap_doubles = 0;         // adjoint: per-strip frontier snapshots
     int64_t ckpt_doubles = 0;         // adjoint: wave-state checkpoints
     int64_t pool_points = 0;
-    int bwd_grid = 0;                 // workgroups the adjoint scratch is sized for
+    int bwd_grid = 0;                 // segment buffers the adjoint scratch is sized for
     uint64_t cells = 0;
     int64_t max_cells = 0;            // cells of the largest pair
     sigk_opts opts;
@@ -394,14 +395,34 @@ namespace {
 
 constexpr int kBwdMaxGrid = 2048;
 
-// Workgroups the adjoint's recompute scratch is sized for: those of the
-// adjoint launch on the current device (no more than `tickets`), or
-// kBwdMaxGrid where no device can be queried (workspace sizes asked for on a
-// host without one).  The launch never exceeds it.
+// Whether an adjoint launch of this many strips runs two waves per strip: as
+// long as every wave has a SIMD to itself.  Measured one wave over two, at
+// orders 5-20 and d 3-32: 1.23-1.43 for 78 pairs of 100 points (156 strips) and
+// 36 of 300 (180).
+bool bwd_two_waves(int64_t tickets) { return tickets <= 2 * device_cus(); }
+
+// Segment buffers the adjoint's recompute scratch is sized for: those of the
+// adjoint launch on the current device (two per strip of a two-wave launch,
+// else one per workgroup and no more than `tickets`), or kBwdMaxGrid where no
+// device can be queried (workspace sizes asked for on a host without one).
+// The launch never exceeds it.
 int bwd_scratch_grid(int P, int D, int64_t tickets) {
     const int g = device_wgs(P, D, kKernelBwd);
     const int64_t n = g > 0 ? std::min(g, kBwdMaxGrid) : kBwdMaxGrid;
-    return (int)std::max<int64_t>(std::min<int64_t>(n, tickets), 1);
+    const int64_t one = std::min<int64_t>(n, tickets);
+    return (int)std::max<int64_t>(bwd_two_waves(tickets) ? 2 * tickets : one, 1);
+}
+
+// The adjoint launch over b.ntickets strips with `bufs` segment buffers.
+hipError_t launch_bwd(const Variant* v, const BwdArgs& b, int P, int D, int grid_opt, int bufs,
+                      hipStream_t s) {
+    // (order 24 with d > 16 spills 600 registers there: 0.87 of the one-wave rate)
+    if (grid_opt <= 0 && bwd_two_waves(b.ntickets) && bufs >= 2 * b.ntickets &&
+        !(P > 20 && D > 16))
+        return v->bwd_two(b, (int)std::max<int64_t>(b.ntickets, 1), s);
+    const int grid = grid_opt > 0 ? grid_opt : device_wgs(P, D, kKernelBwd);
+    return v->bwd(b, (int)std::max<int64_t>(std::min<int64_t>(std::min(grid, bufs), b.ntickets), 1),
+                  s);
 }
 
 void plan_layout(sigk_plan& p) {
@@ -962,9 +983,7 @@ int adjoint_pass(const sigk_plan* plan, const Variant* v, const double* pool,
     b.lam_prog = lprog;
     b.gdx = gdx;
     b.scratch = (double*)(base + plan->o_scr);
-    int bgrid = plan->opts.grid > 0 ? plan->opts.grid : device_wgs(plan->P, plan->D, kKernelBwd);
-    bgrid = (int)std::min<int64_t>(std::min(bgrid, plan->bwd_grid), b.ntickets);
-    e = v->bwd(b, std::max(bgrid, 1), s);
+    e = launch_bwd(v, b, plan->P, plan->D, plan->opts.grid, plan->bwd_grid, s);
     if (e != hipSuccess) return device_error(e);
     hipLaunchKernelGGL(chain_kernel, dim3(blocks_for(ngdx)), dim3(256), 0, s, gdx, grad_pool,
                        plan->pool_points, (int)plan->d);
@@ -1521,7 +1540,6 @@ int sigk_pair_backward(const double* x, int64_t lx, const double* y, int64_t ly,
     k.slot_prog = L.slot_prog;
     k.y_gdx = lx * d;
     const int cgrid = std::max(device_wgs(L.P, L.D, kKernelCkpt), 1);
-    const int bgrid = L.bwd_grid;
 
     // 1. the whole pair once: k(x, y), its truncation estimate and the lines
     // (a single block has none: its checkpointing sweep gives the value)
@@ -1573,7 +1591,7 @@ int sigk_pair_backward(const double* x, int64_t lx, const double* y, int64_t ly,
         if (e != hipSuccess) return device_error(e);
         b.f = a;
         b.ntickets = a.ntickets;
-        e = v->bwd(b, (int)std::min<int64_t>(bgrid, b.ntickets), s);
+        e = launch_bwd(v, b, L.P, L.D, 0, L.bwd_grid, s);
         if (e != hipSuccess) return device_error(e);
     }
     hipLaunchKernelGGL(chain2_kernel, dim3(blocks_for(ngdx)), dim3(256), 0, s, gdx, lx, ly,

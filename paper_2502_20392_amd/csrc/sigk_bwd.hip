@@ -1,6 +1,6 @@
 // sigk_bwd.hip -- gradient of kernel values with respect to the paths.
 //
-// Two persistent kernels per (P, D) variant:
+// Persistent kernels per (P, D) variant:
 //   ckpt_kernel: the forward sweep of every strip, keeping (a) the frontier row
 //                each strip reads (one snapshot per strip instead of the single
 //                in-place row), (b) the wave state (left edges and in-flight top
@@ -17,7 +17,9 @@
 //                dL/d(increment) of both paths: the x side through an LDS ring
 //                indexed by column (each column is complete once lane 0 has
 //                passed it), the y side in registers of the row's lane.
-// Both also run the blocks of a long pair (block checkpointing, see BlockGeo):
+//   bwd_two_kernel: the adjoint sweep with a second wave per strip for the
+//                recompute, for launches of few strips.
+// All also run the blocks of a long pair (block checkpointing, see BlockGeo):
 // a block is a small pair whose bottom and left edges come from lines kept by
 // a first sweep and whose top and right edge cotangents come from the blocks
 // processed before it.
@@ -147,6 +149,13 @@ __global__ void __launch_bounds__(kWave)
     }
 }
 
+// Orders a wave's LDS accesses (its lanes exchange data through LDS); the
+// adjoint's waves never need the workgroup barrier for that.
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // A workgroup's segment scratch as a buffer resource: rows of 64 doubles,
 // one per lane.  The lane's column goes in the vector offset and the row
 // (step and coefficient) in the scalar offset, so stepping through the rows
@@ -226,7 +235,10 @@ struct StripBwd {
     double gy[D];
     Recip<P, false> R;  // scalar or rematerialised constants: registers are scarce here
     int dx_lo, lin_lo, bin_chunk;
-    SegScratch scr;  // kCkptEvery x P recomputed bottom-edge rows, then as many left-edge rows
+    // kCkptEvery x P recomputed bottom-edge rows, then as many left-edge rows (a
+    // smooth segment of the two-wave kernel: P rows of right edges after it);
+    // two such buffers for the two-wave kernel
+    SegScratch scr;
     unsigned long long* cells;  // per-workgroup tallies (cells, algorithmic flops)
     unsigned long long* flops;
     const double* ck;
@@ -253,21 +265,24 @@ struct StripBwd {
         : b(b_), a(b_.f), g(g_), L(L_), s(s_) {}
 
     // Increments of x in steps of kCkptEvery columns, descending, so that the
-    // ring holds [t0-63, t0+kCkptEvery) for segment t0 (and never more than
-    // 63 + chunk columns of pending dL/d(dx) share its slots).
+    // ring holds [t0-63, t0+kCkptEvery) for segment t0 (the recomputing wave of
+    // the two-wave kernel works one segment lower: 96 columns in all), zero
+    // outside the grid's columns: there the maps run with c = 0, which keeps
+    // every right edge and every zero cotangent, and need no per-lane test.
     __device__ void load_dx_down_to(int lo_needed) {
         const int lane = lane_id();
-        while (dx_lo > lo_needed && dx_lo > 0) {
-            const int c0 = max(dx_lo - kCkptEvery, 0);
+        while (dx_lo > lo_needed) {
+            const int c0 = dx_lo - kCkptEvery;
             const int col = c0 + lane;
             if (col < dx_lo && col < m) {
-                const double* xp = g.x + (int64_t)col * a.d;
+                const double* xp = g.x + (int64_t)max(col, 0) * a.d;
 #pragma unroll
                 for (int ch = 0; ch < D; ++ch)
-                    L.dx(ch, ring_slot_of<ARB>(col)) = ch < a.d ? xp[a.d + ch] - xp[ch] : 0.0;
+                    L.dx(ch, ring_slot_of<ARB>(col)) =
+                        ch < a.d && col >= 0 ? xp[a.d + ch] - xp[ch] : 0.0;
             }
             dx_lo = c0;
-            __syncthreads();
+            wave_sync();
         }
     }
 
@@ -288,24 +303,27 @@ struct StripBwd {
             for (int k = 0; k < NB; ++k)
                 if (lane + k * kWave < nc * P) dst[lane + k * kWave] = v[k];
             lin_lo = c0;
-            __syncthreads();
+            wave_sync();
         }
         return true;
     }
 
+    // (steps past the last column read the last chunk's rows: any finite values)
     __device__ void load_bin(int chunk) {
+        if (chunk == bin_chunk) return;
         const int CH = ACH;
         const int lane = lane_id();
         const int c0 = chunk * CH;
         const int nc = min(CH, m - c0);
         if (has_below) {
             const double* src = snap_in + (int64_t)c0 * P;
-            for (int e = lane; e < nc * P; e += kWave) L.bin[e] = src[e];
+            // (0 past the last column: read by lanes past the end of their row)
+            for (int e = lane; e < CH * P; e += kWave) L.bin[e] = e < nc * P ? src[e] : 0.0;
         } else {
             for (int e = lane; e < CH * P; e += kWave) L.bin[e] = (e % P) == 0 ? 1.0 : 0.0;
         }
         bin_chunk = chunk;
-        __syncthreads();
+        wave_sync();
     }
 
     // columns [c0, c1) are final: publish the bottom-edge cotangents to the
@@ -313,7 +331,7 @@ struct StripBwd {
     __device__ void flush_cols(int c0, int c1) {
         const int CH = ACH;
         const int lane = lane_id();
-        __syncthreads();
+        wave_sync();
         const int nc = c1 - c0;
         if (has_below) {
             double* dst = lam_row + (int64_t)c0 * P;
@@ -331,7 +349,7 @@ struct StripBwd {
             }
         }
         (void)CH;
-        __syncthreads();
+        wave_sync();
     }
 
     // depth record of the chunk of step t: depth + kRoughFlag if rough
@@ -344,35 +362,53 @@ struct StripBwd {
     double lBst[P];    // left-edge cotangent carried along the row
     int topl;          // lane whose top-edge cotangent comes from outside the wave
 
-    // Depth dispatch: one specialised segment loop per Neumann depth.
-    template <int Q>
-    __device__ __forceinline__ void segment_at_depth(int q, bool rough, int t0, int t1) {
-        if constexpr (Q < P - 1) {
+    // Depth dispatch: one specialised segment loop per Neumann depth.  what:
+    // 1 recompute, 2 adjoint, 3 both (buf: the scratch buffer's first row).
+    template <int Q, int what>
+    __device__ __forceinline__ void segment_at_depth(int q, bool rough, int t0, int t1, int buf) {
+        if constexpr (Q >= 0 && Q < P - 1) {
             if (q > Q) {
-                segment_at_depth<Q + 1>(q, rough, t0, t1);
+                segment_at_depth<Q + 1, what>(q, rough, t0, t1, buf);
                 return;
             }
         }
-        if (t0 >= kWave && t1 <= m - 1)
-            segment<Q, true>(q, rough, t0, t1);
-        else
-            segment<Q, false>(q, rough, t0, t1);
+        if constexpr (what == 1) {
+            double B[P];
+            recompute<Q, true>(q, rough, t0, t1, buf, B);
+        } else if constexpr (P == 12 && D == 32) {
+            // (one copy of the recompute for both kinds of segment: here the
+            // compiler keeps the loops' arrays in memory otherwise, 4 times
+            // slower; elsewhere two copies are up to 4% faster)
+            double B[P];
+            if constexpr (what == 3) recompute<Q, false>(q, rough, t0, t1, buf, B);
+            if (t0 >= kWave && t1 <= m - 1)
+                adjoint<Q, true, what == 2>(q, rough, t0, t1, buf, B);
+            else
+                adjoint<Q, false, what == 2>(q, rough, t0, t1, buf, B);
+        } else if (P <= 12 && t0 >= kWave && t1 <= m - 1) {
+            half_or_both<Q, P <= 12, what>(q, rough, t0, t1, buf);
+        } else {
+            half_or_both<Q, false, what>(q, rough, t0, t1, buf);
+        }
+    }
+    template <int Q, bool IN, int what>
+    __device__ __forceinline__ void half_or_both(int q, bool rough, int t0, int t1, int buf) {
+        double B[P];
+        if constexpr (what == 3) recompute<Q, false>(q, rough, t0, t1, buf, B);
+        adjoint<Q, IN, what == 2>(q, rough, t0, t1, buf, B);
     }
 
-    // One segment [t0, t1) of kCkptEvery steps: recompute it forward from its
-    // checkpoint, storing each step's bottom edges, then run the adjoint steps
-    // last to first.  Q >= 0: depth fixed at compile time (== q); Q < 0: q.
-    // rough: the left edges are stored too (second half of the scratch) and
-    // read back instead of recovered from the right edges.  IN: every cell
-    // of the segment is inside the strip's columns and none is in its first
-    // or last column (t0 >= 64, t1 <= m - 1), so the per-lane tests for the
-    // row ends, the corner seed and the block lines drop out.
-    template <int Q, bool IN>
-    __device__ void segment(int q, bool rough, int t0, int t1) {
+    // One segment [t0, t1) of kCkptEvery steps, recomputed forward from its
+    // checkpoint, each step's bottom edges stored.  Q >= 0: depth fixed at
+    // compile time (== q); Q < 0: q.  rough: the left edges are stored too
+    // (second half of the buffer).  On return B holds the right edges after
+    // the segment (HAND: left in the buffer for another wave).
+    template <int Q, bool HAND>
+    __device__ void recompute(int q, bool rough, int t0, int t1, int buf, double (&B)[P]) {
         const int lane = lane_id();
         const int CH = ACH;
         const int W = kCkptEvery;
-        double B[P], Ac[P];
+        double Ac[P];
         {
             const double* src = ck + (int64_t)(t0 / W) * (2 * P * kWave);
 #pragma unroll
@@ -384,17 +420,6 @@ struct StripBwd {
         RingPos<ARB> rp;
         rp.set(t0 - lane);
         for (int t = t0; t < t1; ++t) {
-            const int col = t - lane;
-            if (!IN && col == 0) {
-                if (left != nullptr && lane_ok) {
-                    const double* lp = left + ((int64_t)s * kWave + lane) * P;
-#pragma unroll
-                    for (int i = 0; i < P; ++i) B[i] = lp[i];
-                } else {
-#pragma unroll
-                    for (int i = 0; i < P; ++i) B[i] = i == 0 ? 1.0 : 0.0;
-                }
-            }
             double c0 = 0.0, c1 = 0.0;
 #pragma unroll
             for (int ch = 0; ch < D; ch += 2) {
@@ -403,7 +428,7 @@ struct StripBwd {
             }
             rp.next();
             const double c = c0 + c1;
-            const int row0 = (t - t0) * P;
+            const int row0 = buf + (t - t0) * P;
             if (rough) {
 #pragma unroll
                 for (int i = 0; i < P; ++i) scr.store(kCkptEvery * P + row0 + i, B[i]);
@@ -428,19 +453,44 @@ struct StripBwd {
                 for (int i = 0; i < P; ++i) scr.store(row0 + i, A[i]);
                 cell_map<P>(A, B, c, An, Bn, Q >= 0 ? Q : q, R);
             }
-            // past the end of the row B keeps the row's last right edge
-            const bool live = IN || col < m;
+            // (past the end of the row c = 0: B keeps the row's last right edge)
 #pragma unroll
             for (int i = 0; i < P; ++i) {
-                B[i] = live ? Bn[i] : B[i];
+                B[i] = Bn[i];
                 Ac[i] = An[i];
             }
         }
-        // adjoint over the segment, last step first; B walks back from the
-        // right edge after the segment to each cell's left edge
+        if (HAND && !rough) {
+#pragma unroll
+            for (int i = 0; i < P; ++i) scr.store(buf + kCkptEvery * P + i, B[i]);
+        }
+    }
+
+    // The adjoint over the segment, last step first; B walks back from the
+    // right edges after the segment to each cell's left edge (rough: the left
+    // edges are read back).  IN: every cell of the segment is inside the
+    // strip's columns and none is in its first or last column (t0 >= 64,
+    // t1 <= m - 1), so the per-lane tests for the row ends, the corner seed and
+    // the block lines drop out.  HAND: recomputed by another wave, so the right
+    // edges come from the buffer; each step's bottom edges are then loaded a
+    // step ahead (a lone wave has nothing else to cover the load).
+    template <int Q, bool IN, bool HAND>
+    __device__ void adjoint(int q, bool rough, int t0, int t1, int buf, double (&B)[P]) {
+        const int lane = lane_id();
+        const int CH = ACH;
         const unsigned long long fl =
             (unsigned long long)(adjoint_flops(P, Q >= 0 ? Q : q, a.d) +
                                  cell_flops(P, Q >= 0 ? Q : q, a.d));
+        double ahead[HAND ? P : 1];
+        if constexpr (HAND) {
+            if (!rough) {
+#pragma unroll
+                for (int i = 0; i < P; ++i) B[i] = scr.load(buf + kCkptEvery * P + i);
+            }
+#pragma unroll
+            for (int i = 0; i < P; ++i) ahead[i] = scr.load(buf + (t1 - 1 - t0) * P + i);
+        }
+        RingPos<ARB> rp;
         rp.set(t1 - 1 - lane);
         for (int t = t1 - 1; t >= t0; --t) {
             const int col = t - lane;
@@ -450,13 +500,18 @@ struct StripBwd {
                 *cells += cnt;
                 *flops += cnt * fl;
             }
-            const int row0 = (t - t0) * P;
+            const int row0 = buf + (t - t0) * P;
             double A[P];
 #pragma unroll
-            for (int i = 0; i < P; ++i) A[i] = scr.load(row0 + i);
+            for (int i = 0; i < P; ++i) A[i] = HAND ? ahead[HAND ? i : 0] : scr.load(row0 + i);
             if (rough) {
 #pragma unroll
                 for (int i = 0; i < P; ++i) B[i] = scr.load(kCkptEvery * P + row0 + i);
+            }
+            if constexpr (HAND) {
+                const int nrow = t > t0 ? row0 - P : row0;
+#pragma unroll
+                for (int i = 0; i < P; ++i) ahead[i] = scr.load(nrow + i);
             }
             double dxv[D];
             double c0 = 0.0, c1 = 0.0;
@@ -488,26 +543,22 @@ struct StripBwd {
                     f = f * R(i + 1);
                 }
             }
-            if (!IN && col == m - 1) {
-                if (right_in && lane_ok) {
-                    const double* lp = lamv + ((int64_t)s * kWave + lane) * P;
+            // (past the end of the row every cotangent stays 0: c = 0 there)
+            if (!IN && right_in && col == m - 1 && lane_ok) {
+                const double* lp = lamv + ((int64_t)s * kWave + lane) * P;
 #pragma unroll
-                    for (int i = 0; i < P; ++i) lBst[i] = lp[i];
-                } else {
-#pragma unroll
-                    for (int i = 0; i < P; ++i) lBst[i] = 0.0;
-                }
+                for (int i = 0; i < P; ++i) lBst[i] = lp[i];
             }
             // column 0 on a left line: the left edge is recovered like any
             // other (it is the right edge of the block to the left)
             const bool axis = !IN && col == 0 && left == nullptr;
-            const bool recover = !rough && (IN || col < m);  // rough: B is the stored left edge
             double lA[P], lB[P];
             double gc;
+            // (rough: B is the stored left edge)
             if constexpr (Q >= 0)
-                gc = cell_adjoint_fixed<P, Q>(A, B, c, axis, recover, lAo, lBst, lA, lB, R);
+                gc = cell_adjoint_fixed<P, Q>(A, B, c, axis, !rough, lAo, lBst, lA, lB, R);
             else
-                gc = cell_adjoint<P>(A, B, c, q, axis, recover, lAo, lBst, lA, lB, R);
+                gc = cell_adjoint<P>(A, B, c, q, axis, !rough, lAo, lBst, lA, lB, R);
             if (!act) gc = 0.0;
             if (!IN && left_out && act && col == 0) {
                 double* lp = lamv + ((int64_t)s * kWave + lane) * P;
@@ -537,10 +588,9 @@ struct StripBwd {
         }
     }
 
-    __device__ bool sweep() {
+    // Before the segments: the strip's rows and an empty ring.
+    __device__ void begin() {
         const int lane = lane_id();
-        const int CH = ACH;
-        const int W = kCkptEvery;
         m = g.m;
         const int row0 = s * kWave;
         nrows = min(kWave, g.n - row0);
@@ -556,48 +606,143 @@ struct StripBwd {
                          : 0.0;
             gy[ch] = 0.0;
         }
-        for (int e = lane; e < 2 * D * ARB; e += kWave) L.xg[e] = 0.0;
-        const int top = CH * ((m + CH - 1) / CH);
+        for (int e = (int)threadIdx.x; e < 2 * D * ARB; e += (int)blockDim.x) L.xg[e] = 0.0;
         dx_lo = kCkptEvery * ((m + kCkptEvery - 1) / kCkptEvery);
-        lin_lo = top;
+        lin_lo = ACH * ((m + ACH - 1) / ACH);
         bin_chunk = -1;
-        __syncthreads();
-
-        const int T = m + nrows - 1;
 #pragma unroll
         for (int i = 0; i < P; ++i) {
             lAprev[i] = 0.0;
             lBst[i] = 0.0;
         }
         topl = has_above ? kWave - 1 : nrows - 1;
-        for (int t0 = ((T - 1) / W) * W; t0 >= 0; t0 -= W) {
-            const int t1 = min(t0 + W, T);
-            const int rec = depth_at(t0);
-            const int q = rec % kRoughFlag;
-            const bool rough = rec >= kRoughFlag;
-            load_dx_down_to(max(t0 - (kWave - 1), 0));
-            if (has_above && !load_lin_down_to(max(t0 - (kWave - 1), 0))) return false;
-            if (t0 < m && t0 / CH != bin_chunk) load_bin(t0 / CH);
-            if constexpr (P <= 12)
-                segment_at_depth<0>(q, rough, t0, t1);
-            else
-                segment<-1, false>(q, rough, t0, t1);
-            if (t0 < m && (t0 % CH) == 0) flush_cols(t0, min(t0 + CH, m));
-        }
-        // dL/d(dy_l) of this lane's row
+    }
+
+    // After them: dL/d(dy_l) of this lane's row.
+    __device__ void end() {
         if (lane_ok) {
-            double* gp = gyp + (int64_t)l * a.d;
+            double* gp = gyp + (int64_t)(s * kWave + lane_id()) * a.d;
 #pragma unroll
             for (int ch = 0; ch < D; ++ch)
                 if (ch < a.d) atomicAdd(&gp[ch], gy[ch]);
         }
+    }
+
+    // One wave does both halves of every segment.
+    __device__ bool sweep() {
+        begin();
+        wave_sync();
+        const int T = m + nrows - 1;
+        for (int t0 = ((T - 1) / kCkptEvery) * kCkptEvery; t0 >= 0; t0 -= kCkptEvery) {
+            const int t1 = min(t0 + kCkptEvery, T);
+            const int rec = depth_at(t0);
+            const int q = rec % kRoughFlag;
+            const bool rough = rec >= kRoughFlag;
+            load_dx_down_to(t0 - (kWave - 1));
+            if (has_above && !load_lin_down_to(max(t0 - (kWave - 1), 0))) return false;
+            load_bin(min(t0, m - 1) / ACH);
+            segment_at_depth<(P <= 12 ? 0 : -1), 3>(q, rough, t0, t1, 0);
+            if (t0 < m && (t0 % ACH) == 0) flush_cols(t0, min(t0 + ACH, m));
+        }
+        end();
+        wave_sync();
+        return true;
+    }
+
+    // Two waves of one workgroup: wave 1 recomputes segment k while wave 0 runs
+    // the adjoint of segment k + 1, one barrier per segment.  (Every wave of
+    // the workgroup leaves together: stop is set before a barrier.)
+    __device__ bool sweep_two(int wave, int* stop) {
+        begin();
         __syncthreads();
+        const int T = m + nrows - 1;
+        const int nseg = (T + kCkptEvery - 1) / kCkptEvery;
+        for (int k = nseg - 1; k >= -1; --k) {
+            const int mine = wave == 1 ? k : k + 1;
+            if (mine >= 0 && mine < nseg) {
+                const int t0 = mine * kCkptEvery, t1 = min(t0 + kCkptEvery, T);
+                const int rec = depth_at(t0);
+                const int q = rec % kRoughFlag;
+                const bool rough = rec >= kRoughFlag;
+                const int buf = (mine & 1) * 2 * kCkptEvery * P;
+                if (wave == 1) {
+                    load_dx_down_to(t0 - (kWave - 1));
+                    load_bin(min(t0, m - 1) / ACH);
+                    segment_at_depth<(P <= 12 ? 0 : -1), 1>(q, rough, t0, t1, buf);
+                    __builtin_amdgcn_s_waitcnt(0);  // the buffer is written
+                } else if (has_above && !load_lin_down_to(max(t0 - (kWave - 1), 0))) {
+                    if (lane_id() == 0) *stop = 1;
+                } else {
+                    segment_at_depth<(P <= 12 ? 0 : -1), 2>(q, rough, t0, t1, buf);
+                    if (t0 < m && (t0 % ACH) == 0) flush_cols(t0, min(t0 + ACH, m));
+                }
+            }
+            __syncthreads();
+            if (uniform(*(volatile int*)stop)) return false;
+        }
+        if (wave == 0) end();
         return true;
     }
 };
 
+// Points S at strip `strip` of pair (or block slot) `pair`.
 template <int P, int D>
-__global__ void __launch_bounds__(kWave) bwd_kernel(BwdArgs b) {
+__device__ __forceinline__ void place_strip(StripBwd<P, D>& S, const BwdArgs& b, const Geo& g,
+                                            const BlockRef& r, int pair, int strip) {
+    const FwdArgs& a = b.f;
+    S.ck = b.ckpt + g.ckpt + (int64_t)strip * ckpt_strip_doubles(g.m, P);
+    S.ckq = S.ck + ckpt_states(g.m) * 2 * P * kWave;
+    if (a.mode == kModeTable) {
+        const PairDesc& pd = a.desc[pair];
+        S.snap_in = b.snap + pd.snap_off + (int64_t)strip * g.m * P;
+        S.lam_row = b.lam_front + pd.front_off;
+        S.lam_prog = b.lam_prog + pd.prog_off;
+        S.seed_scale = b.grad_out[pair];
+        S.gxp = b.gdx + pd.x_off;
+        S.gyp = b.gdx + pd.y_off;
+    } else {
+        const BlockGeo& k = a.blk;
+        S.snap_in = (strip == 0 && r.bot) ? r.bot
+                                          : b.snap + g.front + (int64_t)strip * g.m * P;
+        S.lam_row = b.lam_front + (int64_t)r.J * k.cb * P;
+        S.lam_prog = b.lam_prog + g.prog;
+        // the grid's corner cell belongs to the top-right block
+        S.seed_scale = (!r.above && !r.right) ? b.grad_out[0] : 0.0;
+        S.gxp = b.gdx + (int64_t)r.J * k.cb * a.d;
+        S.gyp = b.gdx + k.y_gdx + (int64_t)r.I * k.rb * a.d;
+        S.left = r.left;
+        S.below_line = r.bot != nullptr;
+        S.above_blk = r.above;
+        S.lamv = b.lam_v + (int64_t)r.I * k.rb * P;
+        S.right_in = r.right;
+        S.left_out = r.J > 0;
+    }
+}
+
+// Pair, strip and geometry of ticket t; 1: run it, 0: skip it, -1: no more.
+template <int P>
+__device__ __forceinline__ int take_ticket(const BwdArgs& b, unsigned t, int& pair, int& strip,
+                                           Geo& g, BlockRef& r) {
+    const FwdArgs& a = b.f;
+    if (a.mode == kModeTable) {
+        pair = b.tickets[t].pair;
+        strip = b.tickets[t].strip;
+        if (pair < 0) return -1;  // unused slots close a table built on the device
+        g = resolve(a, pair, P, 0);
+        return 1;
+    }
+    // kModeBlock: the blocks of one anti-diagonal, strips top-down
+    pair = (int)(t % (unsigned)a.blk.nb);
+    strip = a.blk.kb - 1 - (int)(t / (unsigned)a.blk.nb);
+    g = resolve_block(a, pair, P, r);
+    return strip * kWave >= g.n ? 0 : 1;  // the top block row has fewer strips
+}
+
+// (two waves per SIMD at orders up to 6 with d <= 8: the scheduler otherwise
+// takes a few registers more than 256 at order 6, 17% slower)
+template <int P, int D>
+__global__ void __launch_bounds__(kWave)
+    __attribute__((amdgpu_waves_per_eu(P <= 6 && D <= 8 ? 2 : 1))) bwd_kernel(BwdArgs b) {
     __shared__ LdsBwd<P, D> L;
     const FwdArgs& a = b.f;
     const int lane = lane_id();
@@ -612,52 +757,63 @@ __global__ void __launch_bounds__(kWave) bwd_kernel(BwdArgs b) {
         int pair, strip;
         Geo g;
         BlockRef r;
-        if (a.mode == kModeTable) {
-            pair = b.tickets[t].pair;
-            strip = b.tickets[t].strip;
-            if (pair < 0) break;  // unused slots close a table built on the device
-            g = resolve(a, pair, P, 0);
-        } else {
-            // kModeBlock: the blocks of one anti-diagonal, strips top-down
-            pair = (int)(t % (unsigned)a.blk.nb);
-            strip = a.blk.kb - 1 - (int)(t / (unsigned)a.blk.nb);
-            g = resolve_block(a, pair, P, r);
-            if (strip * kWave >= g.n) continue;  // the top block row has fewer strips
-        }
+        const int todo = take_ticket<P>(b, t, pair, strip, g, r);
+        if (todo < 0) break;
+        if (todo == 0) continue;
         StripBwd<P, D> S(b, g, L, strip);
         S.scr.init(scratch, 2 * kCkptEvery * P);
         S.cells = &cells;
         S.flops = &flops;
-        S.ck = b.ckpt + g.ckpt + (int64_t)strip * ckpt_strip_doubles(g.m, P);
-        S.ckq = S.ck + ckpt_states(g.m) * 2 * P * kWave;
-        if (a.mode == kModeTable) {
-            const PairDesc& pd = a.desc[pair];
-            S.snap_in = b.snap + pd.snap_off + (int64_t)strip * g.m * P;
-            S.lam_row = b.lam_front + pd.front_off;
-            S.lam_prog = b.lam_prog + pd.prog_off;
-            S.seed_scale = b.grad_out[pair];
-            S.gxp = b.gdx + pd.x_off;
-            S.gyp = b.gdx + pd.y_off;
-        } else {
-            const BlockGeo& k = a.blk;
-            S.snap_in = (strip == 0 && r.bot) ? r.bot
-                                              : b.snap + g.front + (int64_t)strip * g.m * P;
-            S.lam_row = b.lam_front + (int64_t)r.J * k.cb * P;
-            S.lam_prog = b.lam_prog + g.prog;
-            // the grid's corner cell belongs to the top-right block
-            S.seed_scale = (!r.above && !r.right) ? b.grad_out[0] : 0.0;
-            S.gxp = b.gdx + (int64_t)r.J * k.cb * a.d;
-            S.gyp = b.gdx + k.y_gdx + (int64_t)r.I * k.rb * a.d;
-            S.left = r.left;
-            S.below_line = r.bot != nullptr;
-            S.above_blk = r.above;
-            S.lamv = b.lam_v + (int64_t)r.I * k.rb * P;
-            S.right_in = r.right;
-            S.left_out = r.J > 0;
-        }
+        place_strip<P, D>(S, b, g, r, pair, strip);
         if (!S.sweep()) break;
     }
     if (lane == 0) {
+        atomicAdd(&a.hdr->bwd_cells, cells);
+        atomicAdd(&a.hdr->bwd_flops, flops);
+    }
+}
+
+// The same with two waves per strip (sweep_two), for launches of so few strips
+// that every wave has a SIMD to itself: the chain then runs at the adjoint's
+// instructions per step and not at those of recompute and adjoint together
+// (order 10: about 900 and 380).  Gram matrix of 16 paths of 100 points with its
+// gradient, order 10: 1179 -> 1001 us; 20,001-point pair, order 5: 81.5 -> 63.0
+// ms.  With more strips than that the
+// recomputing waves would take the place of working ones.
+template <int P, int D>
+__global__ void __launch_bounds__(2 * kWave) bwd_two_kernel(BwdArgs b) {
+    __shared__ LdsBwd<P, D> L;
+    __shared__ int stop, ticket;
+    const FwdArgs& a = b.f;
+    const int lane = lane_id();
+    const int wave = uniform((int)(threadIdx.x >> 6));
+    double* scratch = b.scratch + (int64_t)blockIdx.x * (4 * kCkptEvery * P * kWave);
+    unsigned long long cells = 0, flops = 0;
+    if (threadIdx.x == 0) stop = 0;
+    for (;;) {
+        __syncthreads();  // both waves are done with the previous strip
+        if (threadIdx.x == 0) {
+            int t = (int)atomicAdd(&a.hdr->ticket2, 1u);
+            if ((int64_t)t >= b.ntickets || (load_status(a.hdr) & SIGK_ERR_WATCHDOG)) t = -1;
+            ticket = t;
+        }
+        __syncthreads();
+        const int t = uniform(ticket);
+        if (t < 0) break;
+        int pair, strip;
+        Geo g;
+        BlockRef r;
+        const int todo = take_ticket<P>(b, (unsigned)t, pair, strip, g, r);
+        if (todo < 0) break;
+        if (todo == 0) continue;
+        StripBwd<P, D> S(b, g, L, strip);
+        S.scr.init(scratch, 4 * kCkptEvery * P);
+        S.cells = &cells;
+        S.flops = &flops;
+        place_strip<P, D>(S, b, g, r, pair, strip);
+        if (!S.sweep_two(wave, &stop)) break;
+    }
+    if (threadIdx.x == 0) {
         atomicAdd(&a.hdr->bwd_cells, cells);
         atomicAdd(&a.hdr->bwd_flops, flops);
     }
@@ -687,6 +843,11 @@ int SIGK_NAME(occupancy_lines_, SIGK_P, SIGK_D)() {
 
 hipError_t SIGK_NAME(launch_bwd_, SIGK_P, SIGK_D)(const BwdArgs& b, int grid, hipStream_t s) {
     hipLaunchKernelGGL((bwd_kernel<SIGK_P, SIGK_D>), dim3(grid), dim3(kWave), 0, s, b);
+    return hipGetLastError();
+}
+
+hipError_t SIGK_NAME(launch_bwd_two_, SIGK_P, SIGK_D)(const BwdArgs& b, int grid, hipStream_t s) {
+    hipLaunchKernelGGL((bwd_two_kernel<SIGK_P, SIGK_D>), dim3(grid), dim3(2 * kWave), 0, s, b);
     return hipGetLastError();
 }
 

@@ -219,7 +219,8 @@ struct BwdArgs {
     int* lam_prog;           // adjoint progress counters (columns done from the right)
     double* gdx;             // [sum len][d]: dL/d(increment) at the increment's first point
     double* scratch;         // per workgroup: kCkptEvery x P x 64 recomputed bottom edges,
-                             // then as many left edges (rough segments)
+                             // then as many left edges (rough segments); twice that for
+                             // two waves per strip
 };
 
 // Records the HIP error string for sigk_strerror and returns SIGK_EDEVICE.
@@ -259,6 +260,7 @@ hipError_t launch_delta_gemm(const FwdArgs& a, hipStream_t s);
     int occupancy_lines_##P##_##D(); \
     hipError_t launch_ckpt_##P##_##D(const FwdArgs& a, int grid, hipStream_t s); \
     hipError_t launch_bwd_##P##_##D(const BwdArgs& a, int grid, hipStream_t s); \
+    hipError_t launch_bwd_two_##P##_##D(const BwdArgs& a, int grid, hipStream_t s); \
     int occupancy_ckpt_##P##_##D(); \
     int occupancy_bwd_##P##_##D();
 SIGK_BWD_VARIANTS(SIGK_DECL_BWD)

@@ -109,3 +109,28 @@ def test_truncation_check_batch_sizes(dev, npairs, scale):
             assert c["status"] == int(est > 2.0 ** -36), (at, est, c)
             assert c["cells"] == 64 * npairs and c["order"] == 6, c
             assert abs(c["trunc_est"] - est) <= 1e-12 * est, (est, c)
+
+
+@pytest.mark.parametrize("order,d", [(5, 3), (8, 8), (10, 3), (10, 16), (12, 3), (16, 3), (24, 3)])
+@pytest.mark.parametrize("scale", [0.4, 3.0])
+def test_adjoint_two_waves(dev, order, d, scale):
+    """The adjoint with a second wave for the recompute (few strips) against the
+    one-wave kernel (an explicit grid): rows of one column, one segment, segment
+    and chunk edges, several strips, smooth and rough segments.  The same sums,
+    and atomics in another order: equal to 1e-12 of the largest component."""
+    lens = [(2, 3), (16, 70), (17, 65), (18, 64), (49, 130), (64, 66), (65, 100), (97, 129),
+            (130, 200)]
+    rows = [l for p in lens for l in p]
+    off = np.concatenate([[0], np.cumsum(rows)]).astype(np.int64)
+    pool = np.concatenate([synth.brownian(1, l, d, scale / np.sqrt(d), seed=order + 3 * l + k)[0]
+                           for k, l in enumerate(rows)])
+    pairs = np.arange(len(rows), dtype=np.int32).reshape(-1, 2)
+    go = torch.linspace(-1.0, 1.0, len(pairs), dtype=torch.float64, device=dev)
+    got = []
+    for grid in (0, 7):
+        plan = sk().RaggedPlan(off, pairs, d, order=order, grid=grid, device=dev)
+        got.append(plan.backward(T(pool, dev), go).cpu().numpy())
+        c = sk().counters(plan.ws)
+        assert not c["status"] & ~1, c
+        assert c["bwd_cells"] == sum((a - 1) * (b - 1) for a, b in lens), c
+    assert np.max(np.abs(got[0] - got[1])) <= 1e-12 * np.max(np.abs(got[1]))
