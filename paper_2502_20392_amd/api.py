@@ -272,6 +272,7 @@ class RaggedPlan:
         self.device = torch.device(device)
         self.ws = None
         self._uploaded = None
+        self._one_stream = False  # used in order on one stream only
         self.order = lib.sigk_supported_order(self.opts.order)
 
     def __del__(self):
@@ -298,10 +299,20 @@ class RaggedPlan:
         if self._uploaded is None:
             _lib.check(_lib.load().sigk_plan_upload(self._h, _ptr(self.ws), self.ws.numel(),
                                                     _stream()))
-            # the plan's host tables must outlive the copy
-            torch.cuda.current_stream().synchronize()
+            if not (self._one_stream and self._small_tables()
+                    and not torch.cuda.is_current_stream_capturing()):
+                # the plan's host tables must outlive the copy, and other
+                # streams may use the plan next
+                torch.cuda.current_stream().synchronize()
             self._uploaded = True
         return self.ws
+
+    def _small_tables(self):
+        """Whether sigk_plan_upload sends the tables as kernel arguments (which the
+        launches have taken when it returns): 64 bytes a pair, 16 a strip."""
+        n = ctypes.c_int64()
+        _lib.check(_lib.load().sigk_plan_tickets(self._h, 0, None, 0, ctypes.byref(n)))
+        return 64 * self.npairs + 16 * n.value <= 32768
 
     def run(self, pool, out=None):
         """out[p] = k(pairs[p]) for pool [sum len, d]; no host-device copies (capturable
@@ -666,6 +677,13 @@ def _pool_and_pairs(X, Y, symmetric):
     return pool.contiguous(), offsets, pairs
 
 
+def _own_plan(*args, **kw):
+    """A plan made and used by one autograd call, in order on its stream."""
+    plan = RaggedPlan(*args, **kw)
+    plan._one_stream = True
+    return plan
+
+
 class _AdjointPairs:
     """The pairs of an autograd call that need a gradient.  Without a budget
     (or when every checkpoint fits it) one plan: its checkpointing forward
@@ -679,7 +697,7 @@ class _AdjointPairs:
     def __init__(self, offsets, pairs, d, order, tol, device, budget=None):
         self.offsets, self.pairs, self.d = offsets, pairs, d
         self.order, self.tol, self.device = order, tol, device
-        self.plan = RaggedPlan(offsets, pairs, d, order=order, tol=tol, device=device)
+        self.plan = _own_plan(offsets, pairs, d, order=order, tol=tol, device=device)
         self.groups = None
         if budget is not None and self.plan.bwd_ws_bytes > budget:
             n = len(pairs)
@@ -712,8 +730,8 @@ class _AdjointPairs:
         self._release(self.plan)  # the forward's workspace is not needed any more
         gpool = torch.zeros_like(pool)
         for idx in self.groups:
-            gp = RaggedPlan(self.offsets, self.pairs[idx], self.d, order=self.order, tol=self.tol,
-                            device=self.device)
+            gp = _own_plan(self.offsets, self.pairs[idx], self.d, order=self.order, tol=self.tol,
+                           device=self.device)
             wi = w[torch.from_numpy(idx).to(w.device)].contiguous()
             gp.backward(pool, wi, grad_pool=gpool)
             if tally is not None:
@@ -746,7 +764,7 @@ class _GramFunction(torch.autograd.Function):
             vals = adj.forward(pool)
         else:
             adj = None
-            plan = RaggedPlan(offsets, pairs, X.shape[2], order=order, tol=tol, device=X.device)
+            plan = _own_plan(offsets, pairs, X.shape[2], order=order, tol=tol, device=X.device)
             vals = plan.run(pool)
         ctx.adj = adj
         ctx.check = check
@@ -758,7 +776,7 @@ class _GramFunction(torch.autograd.Function):
         ny = nx if symmetric else Y.shape[0]
         G = torch.empty((nx, ny), dtype=torch.float64, device=X.device)
         if symmetric:
-            ii, jj = pairs[:, 0], pairs[:, 1]
+            ii, jj = torch.triu_indices(nx, nx, device=X.device)  # the order of pairs
             G[ii, jj] = vals
             G[jj, ii] = vals
         else:
@@ -770,10 +788,8 @@ class _GramFunction(torch.autograd.Function):
     @staticmethod
     def backward(ctx, gG):
         gG = gG.contiguous()
-        pairs = ctx.pairs
         if ctx.symmetric:
-            ii = torch.from_numpy(pairs[:, 0].astype(np.int64)).to(gG.device)
-            jj = torch.from_numpy(pairs[:, 1].astype(np.int64)).to(gG.device)
+            ii, jj = torch.triu_indices(gG.shape[0], gG.shape[0], device=gG.device)
             w = gG[ii, jj] + gG[jj, ii]
             w = torch.where(ii == jj, gG[ii, jj], w)
         else:
@@ -842,7 +858,7 @@ class _MMD2Function(torch.autograd.Function):
                 plan = adj.plan
                 vals = adj.forward(pool)
             else:
-                plan = RaggedPlan(offsets, pairs, d, order=order, tol=tol, device=X.device)
+                plan = _own_plan(offsets, pairs, d, order=order, tol=tol, device=X.device)
                 vals = plan.run(pool)
             if tally is not None:
                 tally.add(plan.ws)
