@@ -50,7 +50,8 @@ def _digest(paths, extra):
 # iterative ILP scheduler: on the MMD^2 batch at order 10 the checkpointing
 # sweep ran 6.6% and the adjoint 2.4% faster.  Where three waves share a SIMD
 # (the forward at orders <= 6 with d <= 8) the default scheduler is faster
-# (the order-5 long pair ran 2-4% slower with it), and the order-5 adjoint was
+# (the order-5 long pair ran 2-4% slower with it, the team kernels at orders 5-6
+# 2-5%), and the order-5 adjoint was
 # unchanged.  The adjoint units keep the default from order 16 up, where this
 # compiler's iterative scheduler fails on some of them.
 ILP_SCHED = ["-mllvm", "-amdgpu-sched-strategy=iterative-ilp"]

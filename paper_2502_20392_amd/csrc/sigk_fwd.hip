@@ -33,12 +33,14 @@ namespace sigk {
 
 template <int P, int D, bool SQ, int CH>
 __global__ void __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(fwd_waves(P, D)))) fwd_kernel(FwdArgs a) {
-    // Two waves per SIMD share the CU's LDS with eight waves: narrower rings
-    // where d > 8, the frontier written 32 (order 12 with d > 8: 16) columns
-    // at a time.
+    // Two waves per SIMD share the CU's LDS with eight waves: a narrower ring
+    // at order 10 where d > 8, the frontier written 32 columns at a time.
     constexpr bool kTwo = fwd_waves(P, D) == 2;
-    constexpr int RB = CH == 64 ? chunk64_ring(P, D) : kTwo && D > 8 ? 96 : ring_cols(P);
-    constexpr int TC = kTwo ? (P == 12 && D > 8 ? 16 : 32) : CH;
+    // The 32-column tile of a variant whose default is 64 keeps that one's ring
+    // and depths: launches may take either and give the same values.
+    constexpr bool kNarrow = CH == 32 && D > 0 && fwd_chunk_cols(P, D) == 64;
+    constexpr int RB = CH == 64 || kNarrow ? chunk64_ring(P, D) : ring_cols(P);
+    constexpr int TC = kTwo ? 32 : CH;
     __shared__ LdsStrip<P, D, CH, RB, TC> L;
     Acc acc;
     const int lane = lane_id();
@@ -60,7 +62,7 @@ __global__ void __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(fwd_
             if (pair < 0) break;  // unused slots close a table built on the device
         }
         Geo g = resolve(a, pair, P, 0);
-        StripCtx<P, D, CH, RB, SQ, false, TC> S(a, g, L, acc, strip);
+        StripCtx<P, D, CH, RB, SQ, false, TC, kNarrow> S(a, g, L, acc, strip);
         S.pair = pair;
         S.Fout = a.frontier + g.front;
         S.Fin = S.Fout;

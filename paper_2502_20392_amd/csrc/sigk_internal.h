@@ -63,20 +63,21 @@ __host__ __device__ constexpr int fwd_ring_cols(int P, int D) {
 // Steps between two tests of a team's counters (sigk_team.h).
 __host__ __device__ constexpr int team_steps(int P) { return P <= 8 ? 16 : 8; }
 // Columns of the ring in the plain and the checkpointing sweep of a variant
-// with 64-column chunks: orders 10-12 with 8 < d <= 16 load increments (and
-// set the Neumann depth) 32 columns at a time, so that two waves per SIMD fit
+// with 64-column chunks: order 10 with 8 < d <= 16 loads increments (and
+// sets the Neumann depth) 32 columns at a time, so that two waves per SIMD fit
 // the CU's LDS.  The same in both sweeps: their values agree bit for bit.
 __host__ __device__ constexpr int chunk64_ring(int P, int D) {
-    return P >= 10 && P <= 12 && D == 16 ? 96 : 128;
+    return P == 10 && D == 16 ? 96 : 128;
 }
 // Waves per SIMD the forward sweep is compiled for.  One wave issues a vector
 // instruction every 5.25 cycles at best, two together one every 4 (measured on
 // chains of FP64 FMAs), so a second wave is worth a quarter of the time where
-// the map fits 256 registers without spills: orders 8-12 with d <= 16 (64 x 64
+// the map fits 256 registers without spills: orders 8-10 with d <= 16, 12 with d <= 8 (64 x 64
 // Gram, length 1024, d 16, order 10: 24.9 ms with one wave, 21.0 with two; at
-// order 20 it spills and 11.2 ms became 17.7).
+// order 20 it spills and 11.2 ms became 17.7; order 12 with d 16 spills 28: large
+// batches 9% faster, small ones up to 13% slower).
 __host__ __device__ constexpr int fwd_waves(int P, int D) {
-    return P <= 6 && D <= 8 ? 3 : (P >= 8 && P <= 12 && D > 0 && D <= 16 ? 2 : 1);
+    return P <= 6 && D <= 8 ? 3 : (P >= 8 && D > 0 && (P <= 10 ? D <= 16 : P == 12 && D <= 8) ? 2 : 1);
 }
 // The other compiled frontier chunk of a (P, D > 0) forward variant: the
 // work-tile width (64 rows x chunk columns) an autotuner may pick instead of

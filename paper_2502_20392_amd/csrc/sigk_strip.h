@@ -39,8 +39,8 @@
 // K (the local series error of the error analysis of App. C, taken at its
 // leading term).  Local errors propagate with O(1) weight relative to K, so
 // they are summed over every cell of the pair: each lane keeps a running sum
-// over its cells; per chunk the wave adds the lanes' sums, each divided by
-// max(1, |K|) of its row where the chunk starts or ends (the smaller), and
+// over its cells, per chunk divided by max(1, |K|) of its row where the chunk
+// starts or ends (the smaller), and
 // each strip adds its share to the pair's total, which the host-side launch
 // compares with the pair's budget (SIGK_WARN_TRUNC above it).
 #pragma once
@@ -85,14 +85,15 @@ struct RingPos {
 
 // D > 0: the channel bucket (d <= D, increments in LDS and registers);
 // D = 0: the cell coefficients come from a field computed beforehand.
-// XC: columns per increment load, the whole chunk where the ring holds it, else 32.
-template <int CH, int RB>
-constexpr int inc_chunk = RB >= CH + kWave - 1 ? CH : 32;
+// Columns per increment load and Neumann depth: 64 where a 128-column ring
+// serves 64-column chunks, or 32-column ones that must give the same depths
+// (wide), else 32.
+template <int CH, int RB, bool wide = false>
+constexpr int inc_chunk = RB >= 64 + kWave - 1 && (CH == 64 || wide) ? 64 : 32;
 
 template <int P, int D, int CH, int RB, int TC = CH>
 struct LdsStrip {
-    static_assert(RB >= inc_chunk<CH, RB> + kWave - 1 && CH % inc_chunk<CH, RB> == 0 &&
-                      CH % TC == 0,
+    static_assert(RB >= 32 + kWave - 1 && CH % TC == 0,
                   "the ring must hold the columns a chunk's steps touch");
     // D > 0: increments of x, [channel][ring slot]; D = 0: the chunk's cell
     // coefficients, [step][lane] (no LDS beyond what D > 0 needs: every byte
@@ -287,6 +288,27 @@ __device__ __forceinline__ double wave_max(double v) {
     return v;
 }
 
+// Largest of the lanes' values (none negative), by DPP moves.
+template <int ctrl, int rows>
+__device__ __forceinline__ double dpp_or_zero(double v) {
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)b, ctrl, rows, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), ctrl, rows, 0xf, false);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+__device__ __forceinline__ double wave_max_nn(double v) {
+    v = fmax(v, dpp_or_zero<0x111, 0xf>(v));  // row_shr:1
+    v = fmax(v, dpp_or_zero<0x112, 0xf>(v));
+    v = fmax(v, dpp_or_zero<0x114, 0xf>(v));
+    v = fmax(v, dpp_or_zero<0x118, 0xf>(v));
+    v = fmax(v, dpp_or_zero<0x142, 0xa>(v));  // row_bcast:15
+    v = fmax(v, dpp_or_zero<0x143, 0xc>(v));  // row_bcast:31
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_readlane((int)b, 63);
+    const int hi = __builtin_amdgcn_readlane((int)(b >> 32), 63);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+
 __device__ __forceinline__ double wave_sum(double v) {
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o);
@@ -408,9 +430,11 @@ __device__ __forceinline__ void lds_copy(double* dst, const double* src) {
 // the boundary hooks of block checkpointing (left edges from a line, a bottom
 // line for strip 0, right-edge lines written during the sweep).
 // TC: columns staged per frontier write.
-template <int P, int D, int CH, int RB, bool SQ = false, bool BLK = false, int TC = CH>
+template <int P, int D, int CH, int RB, bool SQ = false, bool BLK = false, int TC = CH,
+          bool WIDE = false>
 struct StripCtx {
-    static constexpr int XC = inc_chunk<CH, RB>;
+    static constexpr int XC = D > 0 ? inc_chunk<CH, RB, WIDE> : CH;
+    static constexpr int EV = XC < CH ? XC : CH;  // steps between two loads
     const FwdArgs& a;
     Geo& g;
     LdsStrip<P, D, CH, RB, TC>& L;
@@ -431,11 +455,12 @@ struct StripCtx {
     Recip<P> R;
     int pair;           // pair index (truncation estimate slot)
     // truncation estimate: sum of |c| (|A_{P-1}| + |B_{P-1}|) over the lane's
-    // cells of the current chunk, the wave's total of the chunks done, each
-    // relative to the local size of K (wave-uniform), and the binary exponent
-    // of |K| where the lane's current chunk started
+    // cells of the current chunk, the lane's total of the chunks done, each
+    // relative to the local size of K, and the binary exponent of |K| where the
+    // lane's current chunk started
     double tacc, etot;
     int kexp;
+    double tau;         // tau2[lane] (lanes 1..P-1; infinite elsewhere)
     bool padded = false;  // kpad is set: K at the end of the strip's bottom row
     double kpad = 0.0;
     // checkpointing (adjoint support)
@@ -465,7 +490,7 @@ struct StripCtx {
     __device__ __forceinline__ void fold() {
         const double k1 = fabs(B[0]);
         const int e1 = k1 >= 1.0 && k1 <= 1.7e308 ? ilogb(k1) : 0;  // 0 also for NaN
-        etot = uniform_d(etot + wave_sum(ldexp(tacc, -min(kexp, e1))));
+        etot += ldexp(tacc, -min(kexp, e1));
         kexp = e1;
         tacc = 0.0;
     }
@@ -486,11 +511,11 @@ struct StripCtx {
         return true;
     }
 
-    // Bottom edges of steps [c0, c0+XC) past the last column: the constant K at
+    // Bottom edges of steps [c0, c0+EV) past the last column: the constant K at
     // the row's end, as if x stood still there.  Lanes past the end of their
     // row then keep the K of its end (the truncation estimate scales by it).
     __device__ void pad_bottom(int c0) {
-        if (!has_below || c0 + XC <= g.m) return;
+        if (!has_below || c0 + EV <= g.m) return;
         const int lane = lane_id();
         if (!padded) {
             const double* r = &L.bin[((g.m - 1) % CH) * P];
@@ -501,7 +526,7 @@ struct StripCtx {
             padded = true;
             __syncthreads();
         }
-        for (int e = lane; e < XC * P; e += kWave) {
+        for (int e = lane; e < EV * P; e += kWave) {
             const int col = c0 + e / P;
             if (col >= g.m) L.bin[(col % CH) * P + e % P] = e % P == 0 ? kpad : 0.0;
         }
@@ -515,10 +540,8 @@ struct StripCtx {
     // recovery inverts a triangular Toeplitz factor of norm up to e^|c| per
     // step and loses precision over a segment for |c| of order 1 and above).
     __device__ __forceinline__ void set_depth(int c0, double cmax2) {
-        int qq = 0;
-#pragma unroll
-        for (int n = 1; n < P; ++n) qq = cmax2 > a.tau2[n] ? n : qq;
-        q = uniform(qq);
+        const uint64_t need = ballot(cmax2 > tau);  // lane n compares term n
+        q = need ? 63 - __builtin_clzll(need) : 0;
         if (ckq && lane_id() == 0)
             ckq[c0 / XC] = (double)(q + (cmax2 > kRoughC2 ? kRoughFlag : 0));
     }
@@ -549,7 +572,7 @@ struct StripCtx {
         if (c0 < g.m && has_below && !load_frontier(c0, min(CH, g.m - c0))) return false;
         __syncthreads();
         pad_bottom(c0);
-        const double cmax = wave_max(cm);
+        const double cmax = wave_max_nn(cm);
         set_depth(c0, cmax * cmax);
         return true;
     }
@@ -562,6 +585,14 @@ struct StripCtx {
     __device__ bool load_chunk(int c0) {
         if constexpr (D == 0) return load_chunk_field(c0);
         const int lane = lane_id();
+        if constexpr (CH < XC) {
+            if (c0 % XC != 0) {  // the second chunk of an increment load
+                if (has_below && c0 < g.m && !load_frontier(c0, min(CH, g.m - c0))) return false;
+                __syncthreads();
+                pad_bottom(c0);
+                return true;
+            }
+        }
         const int nc = min(XC, g.m - c0);
         const int col = c0 + lane;
         double lo[D > 0 ? D : 1], hi[D > 0 ? D : 1];
@@ -599,7 +630,7 @@ struct StripCtx {
         const int k1 = c0 - (kWave - 1) + lane, k2 = c0 + lane;
         if (k1 >= 0 && k1 < c0 + nc) w = (double)L.nrm2[ring_slot_of<RB>(k1)];
         if (lane < nc) w = fmax(w, (double)L.nrm2[ring_slot_of<RB>(k2)]);
-        set_depth(c0, wave_max(w) * dymax2);
+        set_depth(c0, wave_max_nn(w) * dymax2);
         return true;
     }
 
@@ -787,14 +818,14 @@ struct StripCtx {
         const int m = g.m;
         int t = 0;
         while (t < T) {
-            if ((t % XC) == 0) {
-                fold();
+            if ((t % EV) == 0) {
+                if ((t % XC) == 0) fold();
                 if (!load_chunk(t)) return false;
                 if constexpr (!kAhead && D > 0) rp.set(t - lane_id());
                 if (kAhead) prefetch(t);
             }
             // steps up to the next load, flush point or the end
-            int te = min(T, t - (t % XC) + XC);
+            int te = min(T, t - (t % EV) + EV);
             const bool stage = has_above && t >= kWave - 1;
             if (has_above) {
                 // the top lane finishes column tc at step tc + 63
@@ -839,6 +870,7 @@ struct StripCtx {
         }
         dymax2 = wave_max(n2);
         q = P - 1;
+        tau = lane >= 1 && lane < P ? a.tau2[lane < kMaxP ? lane : 0] : __builtin_inf();
         tacc = 0.0;
         etot = 0.0;
         kexp = 0;
@@ -873,7 +905,7 @@ struct StripCtx {
         if (ck && (T % ck_every) == 0) save_state(T);
         // the strip's share of the pair's truncation estimate
         fold();
-        const double est = etot * inv_factorial<P>();
+        const double est = wave_sum(etot) * inv_factorial<P>();
         if (!isfinite(est)) acc.status |= SIGK_WARN_NONFINITE;
         if (lane == 0 && a.trunc_est) {
             if (a.solo) a.trunc_est[0] = est;

@@ -70,27 +70,6 @@ __host__ __device__ constexpr size_t team_lds_bytes(int W) {
     return 256 + edges + coef;
 }
 
-// Largest of the lanes' values (none negative), by DPP moves.
-template <int ctrl, int rows>
-__device__ __forceinline__ double dpp_or_zero(double v) {
-    const long long b = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)b, ctrl, rows, 0xf, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), ctrl, rows, 0xf, false);
-    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-}
-__device__ __forceinline__ double wave_max_nn(double v) {
-    v = fmax(v, dpp_or_zero<0x111, 0xf>(v));  // row_shr:1
-    v = fmax(v, dpp_or_zero<0x112, 0xf>(v));
-    v = fmax(v, dpp_or_zero<0x114, 0xf>(v));
-    v = fmax(v, dpp_or_zero<0x118, 0xf>(v));
-    v = fmax(v, dpp_or_zero<0x142, 0xa>(v));  // row_bcast:15
-    v = fmax(v, dpp_or_zero<0x143, 0xc>(v));  // row_bcast:31
-    const long long b = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_readlane((int)b, 63);
-    const int hi = __builtin_amdgcn_readlane((int)(b >> 32), 63);
-    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-}
-
 // Workgroup-scope LDS counters.
 __device__ __forceinline__ void lds_publish(int* f, int v) {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
@@ -281,7 +260,7 @@ struct TeamWave {
     bool padded;
     double cn;
     double dymax2;
-    double tau;          // tau2[lane] (lanes 1..P-1; huge elsewhere)
+    double tau;          // tau2[lane] (lanes 1..P-1; infinite elsewhere)
     double tacc, etot;   // as in StripCtx; etot per lane
     int kexp, q;
     Recip<P> R;
@@ -438,7 +417,7 @@ struct TeamWave {
             }
             dymax2 = wave_max(n2);
         }
-        tau = lane >= 1 && lane < P ? a.tau2[lane < kMaxP ? lane : 0] : 1.7e308;
+        tau = lane >= 1 && lane < P ? a.tau2[lane < kMaxP ? lane : 0] : __builtin_inf();
         q = P - 1;
         tacc = 0.0;
         etot = 0.0;

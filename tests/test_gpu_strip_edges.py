@@ -134,3 +134,21 @@ def test_adjoint_two_waves(dev, order, d, scale):
         assert not c["status"] & ~1, c
         assert c["bwd_cells"] == sum((a - 1) * (b - 1) for a, b in lens), c
     assert np.max(np.abs(got[0] - got[1])) <= 1e-12 * np.max(np.abs(got[1]))
+
+
+@pytest.mark.parametrize("order,d", [(5, 3), (10, 3), (10, 16), (12, 3), (12, 16), (16, 3),
+                                     (20, 16)])
+def test_narrow_tile_same_values(dev, order, d):
+    """Where the default tile is 64 columns wide, a plan whose launch is bound by
+    its chains takes the 32-column one by itself: the same Neumann depths and
+    cell maps, so the same bits as either explicit tile."""
+    lens = [(17, 70), (40, 65), (64, 200), (65, 129), (97, 64), (130, 300), (333, 66)]
+    rows = [l for p in lens for l in p]
+    off = np.concatenate([[0], np.cumsum(rows)]).astype(np.int64)
+    pool = np.concatenate([synth.brownian(1, l, d, 0.5 / np.sqrt(d), seed=order + 5 * l + k)[0]
+                           for k, l in enumerate(rows)])
+    pairs = np.arange(len(rows), dtype=np.int32).reshape(-1, 2)
+    assert sk().api.tile_options(order, d) == [64, 32]
+    got = [sk().RaggedPlan(off, pairs, d, order=order, tile=tile, device=dev).run(T(pool, dev))
+           for tile in (0, 32, 64)]
+    assert torch.equal(got[0], got[1]) and torch.equal(got[0], got[2])
