@@ -1,6 +1,6 @@
 """Build the CPU oracle shared library (plain C, gcc).
 
-TEST INFRASTRUCTURE ONLY: the oracle is the checker for the GPU library and is
+TEST INFRASTRUCTURE ONLY: the oracle checks the GPU library and is
 never part of its product path.
 
 The single source is compiled twice, once with REAL = double and once with
