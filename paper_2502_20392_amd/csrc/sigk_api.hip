@@ -187,6 +187,33 @@ int device_wgs(int P, int D, int kind) {
     return value;
 }
 
+// Whether a launch of a variant whose default tile runs two waves per SIMD takes
+// its 32-column tile, which runs one (lone_narrow): where the longest chain of
+// strips outweighs the work over one wave per SIMD, a second wave only slows the
+// chain.  chain and work in steps, the chain with the default tile's lag.  Default
+// tile over this one, order 10, d 16, work over chain 0.4-1.06: 1.14-1.33; 1.21-1.42:
+// 0.92-0.98; 2.3: 0.86 (order 12, d 8: 1.17-1.38, 0.96-1.02, 0.91).
+constexpr double kLoneRatio = 1.1;
+bool lone_tile(int P, int D, const sigk_opts& op, double chain, double work) {
+    return lone_narrow(P, D) && op.tile_cols == 0 && op.grid <= 0 &&
+           !(op.flags & SIGK_FLAG_SQUARE) && kLoneRatio * chain > work / (4.0 * device_cus());
+}
+// Workgroups of a launch on the tile taken here: where its registers would let a
+// second wave onto the SIMDs (order 10, d <= 8), no more than one per SIMD
+// (136 pairs of 1024 points: 2.37 ms with two, 2.04 with one).
+int tile_wgs(int P, int D, const sigk_opts& op, int tile) {
+    const int g = device_wgs(P, D, fwd_kind(P, D, op.flags, tile));
+    return tile != op.tile_cols && lone_narrow(P, D) ? std::min(g, 4 * device_cus()) : g;
+}
+// The same for a Gram call: the tile its one-wave kernel takes.
+int gram_tile(int P, int D, const sigk_opts& op, int64_t strips, int64_t npairs, int64_t m) {
+    const double sweep = (double)(m + kWave - 1);
+    return lone_tile(P, D, op, sweep + (double)(strips - 1) * (64 + kWave - 1),
+                     sweep * (double)(strips * npairs))
+               ? 32
+               : op.tile_cols;
+}
+
 // Compute waves per team of a Gram call's forward sweep (the team kernel), 0
 // for the one-wave kernel.  The team kernel shortens the dependency chain of a
 // pair (a start lag of 64 + team_sub steps per strip against 63 + chunk) but
@@ -209,14 +236,16 @@ int team_waves(int P, int D, const sigk_opts& op, int64_t strips, int64_t npairs
     // a step of one of w waves on a SIMD against a lone wave's (5.25, 7.1 and
     // 9.1 cycles per FP64 instruction measured for 1, 2 and 3)
     auto slow = [](double w) { return 1.0 + 0.37 * std::max(0.0, w - 1.0); };
-    const double cap1 = device_wgs(P, D, kKernelFwd), all1 = (double)(npairs * strips);
+    const bool lone = gram_tile(P, D, op, strips, npairs, m) == 32;
+    const double cap1 = tile_wgs(P, D, op, lone ? 32 : 0);
+    const double all1 = (double)(npairs * strips);
     const double cap_t = device_wgs(P, D, kKernelTeam + W), all_t = (double)(npairs * groups);
     const double f1 = slow(std::min(all1, cap1) / simds);
     const double f_t = slow(std::min(all_t, cap_t) * (W + 1) / simds);
     // the one-wave kernel's chunk round trips, against its steps
     const double trips = P <= 8 ? 1.15 : P <= 12 ? 1.1 : 1.03;
     const double chain1 =
-        trips * (sweep + (double)(strips - 1) * (fwd_chunk_cols(P, D) + kWave - 1));
+        trips * (sweep + (double)(strips - 1) * ((lone ? 32 : fwd_chunk_cols(P, D)) + kWave - 1));
     const double chain_t = sweep + (double)(strips - 1) * lag;
     const double t1 = std::max(chain1 * (all1 <= cap1 ? f1 : 1.0), sweep * all1 / cap1 * f1);
     const double t_t = std::max(chain_t * (all_t <= cap_t ? f_t : 1.0),
@@ -498,6 +527,8 @@ int plan_tile(const sigk_plan& p) {
     if (p.opts.tile_cols != 0 || p.opts.grid > 0 || (p.opts.flags & SIGK_FLAG_SQUARE) ||
         fwd_chunk_cols(p.P, p.D) != 64)
         return p.opts.tile_cols;
+    if (lone_narrow(p.P, p.D))
+        return lone_tile(p.P, p.D, p.opts, (double)p.chain, (double)p.work) ? 32 : 0;
     const double work = (double)p.work / (double)std::max(device_wgs(p.P, p.D, kKernelFwd), 1);
     return (double)p.chain > 1.5 * work ? 32 : 0;
 }
@@ -530,8 +561,7 @@ int fwd_pass(const sigk_plan* plan, const double* pool, double* out, char* base,
     if (!v) return SIGK_EUNSUPPORTED;
     int grid = plan->opts.grid > 0
                    ? plan->opts.grid
-                   : device_wgs(plan->P, plan->D,
-                                fwd_kind(plan->P, plan->D, plan->opts.flags, tile));
+                   : tile_wgs(plan->P, plan->D, plan->opts, tile);
     grid = (int)std::min<int64_t>(grid, a.ntickets);
     hipError_t e = v->fwd(a, std::max(grid, 1), s);
     if (e == hipSuccess && !a.check)
@@ -669,8 +699,10 @@ int sigk_gram(const double* X, int64_t nx, const double* Y, int64_t ny, int64_t 
         const int grid = (int)std::min<int64_t>(device_wgs(P, D, kKernelTeam + team), a.ntickets);
         e = find_team(P, D)->launch(a, std::max(grid, 1), s);
     } else {
-        int grid =
-            op.grid > 0 ? op.grid : device_wgs(P, D, fwd_kind(P, D, op.flags, op.tile_cols));
+        const int tile = gram_tile(P, D, op, L.strips, L.npairs, lx - 1);
+        if (tile != op.tile_cols) v = find_fwd(P, D, op.flags, tile);
+        if (!v) return SIGK_EUNSUPPORTED;
+        int grid = op.grid > 0 ? op.grid : tile_wgs(P, D, op, tile);
         grid = (int)std::min<int64_t>(grid, a.ntickets);
         e = v->fwd(a, std::max(grid, 1), s);
     }

@@ -32,10 +32,10 @@
 namespace sigk {
 
 template <int P, int D, bool SQ, int CH>
-__global__ void __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(fwd_waves(P, D)))) fwd_kernel(FwdArgs a) {
+__global__ void __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(fwd_tile_waves(P, D, CH)))) fwd_kernel(FwdArgs a) {
     // Two waves per SIMD share the CU's LDS with eight waves: a narrower ring
     // at order 10 where d > 8, the frontier written 32 columns at a time.
-    constexpr bool kTwo = fwd_waves(P, D) == 2;
+    constexpr bool kTwo = fwd_tile_waves(P, D, CH) == 2;
     // The 32-column tile of a variant whose default is 64 keeps that one's ring
     // and depths: launches may take either and give the same values.
     constexpr bool kNarrow = CH == 32 && D > 0 && fwd_chunk_cols(P, D) == 64;

@@ -79,6 +79,17 @@ __host__ __device__ constexpr int chunk64_ring(int P, int D) {
 __host__ __device__ constexpr int fwd_waves(int P, int D) {
     return P <= 6 && D <= 8 ? 3 : (P >= 8 && D > 0 && (P <= 10 ? D <= 16 : P == 12 && D <= 8) ? 2 : 1);
 }
+// The 32-column tile of a variant whose 64-column default runs two waves per
+// SIMD is compiled for one: launches bound by their chains of strips take it
+// (lone_tile in sigk_api.hip), and there a second wave on the SIMD makes every
+// step of the chain a third longer (136 pairs of 1024 points, order 10, d 16:
+// 2.14 ms with one wave per SIMD, 2.68 with two).
+__host__ __device__ constexpr bool lone_narrow(int P, int D) {
+    return P >= 8 && D > 0 && fwd_waves(P, D) == 2 && fwd_chunk_cols(P, D) == 64;
+}
+__host__ __device__ constexpr int fwd_tile_waves(int P, int D, int CH) {
+    return CH == 32 && lone_narrow(P, D) ? 1 : fwd_waves(P, D);
+}
 // The other compiled frontier chunk of a (P, D > 0) forward variant: the
 // work-tile width (64 rows x chunk columns) an autotuner may pick instead of
 // the default, 32 where the default is 64 and 64 where it is 32.  The same

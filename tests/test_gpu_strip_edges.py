@@ -152,3 +152,15 @@ def test_narrow_tile_same_values(dev, order, d):
     got = [sk().RaggedPlan(off, pairs, d, order=order, tile=tile, device=dev).run(T(pool, dev))
            for tile in (0, 32, 64)]
     assert torch.equal(got[0], got[1]) and torch.equal(got[0], got[2])
+
+
+@pytest.mark.parametrize("order,d,nx,ny,lx,ly", [(10, 3, 24, 0, 257, 257), (10, 16, 40, 9, 131, 300),
+                                                 (12, 8, 25, 13, 193, 322), (12, 3, 24, 0, 190, 190)])
+def test_gram_tile_rule_same_values(dev, order, d, nx, ny, lx, ly):
+    """A Gram call with more strips than SIMDs whose chains still bound it takes the
+    narrow tile by itself (variants of two waves per SIMD): the bits of the wide one."""
+    X = T(synth.brownian(nx, lx, d, 0.5 / np.sqrt(d), seed=order + lx), dev)
+    Y = T(synth.brownian(ny, ly, d, 0.5 / np.sqrt(d), seed=order + ly), dev) if ny else None
+    got = sk().gram(X, Y, order=order)
+    for tile in (32, 64):
+        assert torch.equal(got, sk().gram(X, Y, order=order, tile=tile)), tile
