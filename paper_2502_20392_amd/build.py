@@ -27,7 +27,7 @@ FLAGS = EXTRA + ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}", "-munsa
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wall", "-Wno-unused-function", "-Wno-unused-variable", "-I", INCLUDE]
 HEADERS = ["sigk_internal.h", "sigk_device.h", "sigk_strip.h", "sigk_adjoint.h",
-           "sigk_team.h"]
+           "sigk_team.h", "sigk_stop.h"]
 
 
 def _variants(name):

@@ -24,6 +24,7 @@
 // a first sweep and whose top and right edge cotangents come from the blocks
 // processed before it.
 #include "sigk_adjoint.h"
+#include "sigk_stop.h"
 
 #ifndef SIGK_P
 #define SIGK_P 8
@@ -650,9 +651,9 @@ struct StripBwd {
     }
 
     // Two waves of one workgroup: wave 1 recomputes segment k while wave 0 runs
-    // the adjoint of segment k + 1, one barrier per segment.  (Every wave of
-    // the workgroup leaves together: stop is set before a barrier.)
-    __device__ bool sweep_two(int wave, int* stop) {
+    // the adjoint of segment k + 1, one barrier per segment.  (Both waves leave
+    // after the same barrier: sigk_stop.h.)
+    __device__ bool sweep_two(int wave, StopFlags& stop) {
         begin();
         __syncthreads();
         const int T = m + nrows - 1;
@@ -671,14 +672,14 @@ struct StripBwd {
                     segment_at_depth<(P <= 12 ? 0 : -1), 1>(q, rough, t0, t1, buf);
                     __builtin_amdgcn_s_waitcnt(0);  // the buffer is written
                 } else if (has_above && !load_lin_down_to(max(t0 - (kWave - 1), 0))) {
-                    if (lane_id() == 0) *stop = 1;
+                    if (lane_id() == 0) stop.raise(k);
                 } else {
                     segment_at_depth<(P <= 12 ? 0 : -1), 2>(q, rough, t0, t1, buf);
                     if (t0 < m && (t0 % ACH) == 0) flush_cols(t0, min(t0 + ACH, m));
                 }
             }
             __syncthreads();
-            if (uniform(*(volatile int*)stop)) return false;
+            if (uniform(stop.test(k))) return false;
         }
         if (wave == 0) end();
         return true;
@@ -783,13 +784,14 @@ __global__ void __launch_bounds__(kWave)
 template <int P, int D>
 __global__ void __launch_bounds__(2 * kWave) bwd_two_kernel(BwdArgs b) {
     __shared__ LdsBwd<P, D> L;
-    __shared__ int stop, ticket;
+    __shared__ StopFlags stop;
+    __shared__ int ticket;
     const FwdArgs& a = b.f;
     const int lane = lane_id();
     const int wave = uniform((int)(threadIdx.x >> 6));
     double* scratch = b.scratch + (int64_t)blockIdx.x * (4 * kCkptEvery * P * kWave);
     unsigned long long cells = 0, flops = 0;
-    if (threadIdx.x == 0) stop = 0;
+    if (threadIdx.x == 0) stop.clear();
     for (;;) {
         __syncthreads();  // both waves are done with the previous strip
         if (threadIdx.x == 0) {
@@ -811,7 +813,7 @@ __global__ void __launch_bounds__(2 * kWave) bwd_two_kernel(BwdArgs b) {
         S.cells = &cells;
         S.flops = &flops;
         place_strip<P, D>(S, b, g, r, pair, strip);
-        if (!S.sweep_two(wave, &stop)) break;
+        if (!S.sweep_two(wave, stop)) break;
     }
     if (threadIdx.x == 0) {
         atomicAdd(&a.hdr->bwd_cells, cells);
