@@ -106,23 +106,24 @@ int SIGK_NAME(SIGK_OCC, SIGK_P, SIGK_D)() {
 
 #if !SIGK_SQ && !SIGK_ALT
 hipError_t SIGK_NAME(launch_team_, SIGK_P, SIGK_D)(const FwdArgs& a, int grid, hipStream_t s) {
-    const size_t lds = team_lds_bytes<SIGK_P, SIGK_D>(a.team);
-    hipError_t e = hipFuncSetAttribute((const void*)team_kernel<SIGK_P, SIGK_D>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
     hipLaunchKernelGGL((team_kernel<SIGK_P, SIGK_D>), dim3(grid), dim3(kWave * (a.team + 1)),
-                       lds, s, a);
+                       (team_lds_bytes<SIGK_P, SIGK_D>(a.team)), s, a);
     return hipGetLastError();
 }
 
+// (asked once per device and team size, before any launch of that size.  The
+// kernel's dynamic LDS limit is shared by all host threads: always the largest
+// team's, so that no call lowers it between another's setting and launch)
 int SIGK_NAME(occupancy_team_, SIGK_P, SIGK_D)(int waves) {
-    if (waves < 0) return team_max_waves<SIGK_P, SIGK_D>;
+    constexpr int kMax = team_max_waves<SIGK_P, SIGK_D>;
+    if (waves < 0) return kMax;
     int nb = 0;
-    const size_t lds = team_lds_bytes<SIGK_P, SIGK_D>(waves);
     if (hipFuncSetAttribute((const void*)team_kernel<SIGK_P, SIGK_D>,
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, team_kernel<SIGK_P, SIGK_D>,
-                                                     kWave * (waves + 1), lds) != hipSuccess)
+                            hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)team_lds_bytes<SIGK_P, SIGK_D>(kMax)) != hipSuccess ||
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(
+            &nb, team_kernel<SIGK_P, SIGK_D>, kWave * (waves + 1),
+            team_lds_bytes<SIGK_P, SIGK_D>(waves)) != hipSuccess)
         return 0;
     return nb;
 }

@@ -1,0 +1,32 @@
+"""What the host side launches, recorded without a GPU (launch_recorder.py)."""
+import os
+
+import pytest
+
+from launch_recorder import kernels, record
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+def test_one_lds_limit_per_team_kernel():
+    """The dynamic LDS limit of a team kernel is the same whatever team sizes are
+    launched (it is shared by every host thread), covers each of them, and is not
+    set again by later calls."""
+    lens = [65 + 64 * k + 1 for k in range(1, 12)]
+    jobs = [dict(call="gram", nx=1, lx=n, d=d, order=p)
+            for p, d in ((6, 8), (10, 16), (12, 32), (24, 8), (8, 40)) for n in lens]
+    res = record(jobs + jobs)
+    first, again = res[:len(jobs)], res[len(jobs):]
+    limits, used = {}, {}
+    for r in first:
+        assert r["rc"] == 0
+        for what, name, _, block, lds in r["events"]:
+            if what == "attribute":
+                limits.setdefault(name, set()).add(lds)
+            elif name.startswith("team_kernel"):
+                used.setdefault(name, set()).add((block, lds))
+    assert len(limits) == 5 and all(len(v) == 1 for v in limits.values()), limits
+    for name, sizes in used.items():
+        assert len(sizes) > 1, (name, sizes)  # several team sizes were launched
+        assert max(lds for _, lds in sizes) <= min(limits[name]), name
+    assert not any(e[0] == "attribute" for r in again for e in r["events"])
