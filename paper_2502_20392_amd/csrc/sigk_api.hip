@@ -148,11 +148,21 @@ int fwd_kind(int P, int D, uint32_t flags, int tile) {
                                       : (alt_tile(P, D, tile) ? kKernelFwdT : kKernelFwd);
 }
 
+// CUs of a device (with g_mu held); 256 where it cannot be asked.
+int cus_of(int dev) {
+    if (dev < 64 && g_cus[dev] > 0) return g_cus[dev];
+    int cus = 0;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        cus <= 0)
+        return 256;
+    if (dev < 64) g_cus[dev] = cus;
+    return cus;
+}
 int device_cus() {
     int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev >= 64) return 256;
+    if (hipGetDevice(&dev) != hipSuccess) return 256;
     std::lock_guard<std::mutex> lk(g_mu);
-    return g_cus[dev] > 0 ? g_cus[dev] : 256;
+    return cus_of(dev);
 }
 
 int device_wgs(int P, int D, int kind) {
@@ -161,11 +171,6 @@ int device_wgs(int P, int D, int kind) {
     std::lock_guard<std::mutex> lk(g_mu);
     for (auto& k : g_occ)
         if (k.dev == dev && k.P == P && k.D == D && k.kind == kind) return k.value;
-    if (dev < 64 && g_cus[dev] == 0) {
-        int cus = 0;
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-        g_cus[dev] = cus;
-    }
     int occ = 0;
     if (kind >= kKernelTeam) {
         const TeamVariant* v = find_team(P, D);
@@ -182,7 +187,7 @@ int device_wgs(int P, int D, int kind) {
                 : 0;
     }
     if (occ < 1) occ = 1;
-    int value = occ * (dev < 64 ? g_cus[dev] : 256);
+    int value = occ * cus_of(dev);
     g_occ.push_back({dev, P, D, kind, value});
     return value;
 }

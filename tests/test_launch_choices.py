@@ -30,3 +30,16 @@ def test_one_lds_limit_per_team_kernel():
         assert len(sizes) > 1, (name, sizes)  # several team sizes were launched
         assert max(lds for _, lds in sizes) <= min(limits[name]), name
     assert not any(e[0] == "attribute" for r in again for e in r["events"])
+
+
+@pytest.mark.parametrize("cus", [32, 64, 128])
+def test_first_call_knows_the_device(cus):
+    """On a device of fewer CUs the first call of a process launches what every
+    later one does (the CU count enters the choice of kernel and grid)."""
+    for job in (dict(call="gram", nx=12, lx=300, d=16, order=10),
+                dict(call="gram", nx=9, lx=700, d=3, order=12),
+                dict(call="gram", nx=5, lx=2000, d=3, order=6)):
+        _, first, again, last = record([dict(call="cus", n=cus), job, job, job])
+        for r in (first, again, last):
+            r["events"] = [e for e in r["events"] if e[0] == "launch"]
+        assert first == again == last, (cus, job)
