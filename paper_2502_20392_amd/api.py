@@ -584,7 +584,9 @@ def pair_backward(x, y, grad_out=None, grad_x=None, grad_y=None, order=12, tol=N
                   ws=None):
     """k(x, y) and its gradient for one (long) pair by block checkpointing
     (sigk_pair_backward): grad_x += grad_out dk/dx, grad_y += grad_out dk/dy.
-    grad_out: a one-element CUDA tensor (default 1).  Returns (k, grad_x, grad_y)."""
+    grad_out: a one-element CUDA tensor (default 1).  Returns (k, grad_x, grad_y).
+    Without block sizes the largest square blocks that fit the workspace are taken,
+    up to 4 GiB; ``ws`` may be any size from the least-memory blocks' up."""
     x = _check_paths(x, "x", 2)
     y = _check_paths(y, "y", 2)
     if x.shape[1] != y.shape[1]:
@@ -605,12 +607,31 @@ def pair_backward(x, y, grad_out=None, grad_x=None, grad_y=None, order=12, tol=N
     _lib.check(lib.sigk_pair_backward_workspace_size(x.shape[0], y.shape[0], x.shape[1],
                                                      block_rows, block_cols, ctypes.byref(o),
                                                      ctypes.byref(nb)))
-    w = _user_ws(ws, nb.value, dev)
     k = torch.empty((), dtype=torch.float64, device=dev)
-    _lib.check(lib.sigk_pair_backward(_ptr(x), x.shape[0], _ptr(y), y.shape[0], x.shape[1],
+
+    def call(w):
+        return lib.sigk_pair_backward(_ptr(x), x.shape[0], _ptr(y), y.shape[0], x.shape[1],
                                       _ptr(grad_out), block_rows, block_cols, ctypes.byref(o),
                                       _ptr(k), _ptr(grad_x), _ptr(grad_y), _ptr(w), w.numel(),
-                                      _stream()))
+                                      _stream())
+
+    # a caller's workspace serves from the least-memory blocks up; where the
+    # recommended one cannot be allocated a smaller one may do
+    w = _user_ws(ws, 0, dev) if ws is not None else None
+    rc = call(w) if w is not None else _lib.SIGK_EWORKSPACE
+    nbytes = nb.value
+    while rc == _lib.SIGK_EWORKSPACE:
+        try:
+            w = workspace(nbytes, dev)
+        except torch.cuda.OutOfMemoryError:
+            nbytes //= 2
+            if nbytes < 256:
+                raise
+            continue
+        rc = call(w)
+        if rc == _lib.SIGK_EWORKSPACE and nbytes < nb.value:
+            raise torch.cuda.OutOfMemoryError(f"pair_backward: no workspace within {nbytes} bytes")
+    _lib.check(rc)
     _tls.ws = w
     return k, grad_x, grad_y
 

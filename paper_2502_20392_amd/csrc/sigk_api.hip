@@ -1451,7 +1451,9 @@ int auto_block(int64_t m, int64_t n) {
     return std::min(std::max(r, 64), 16384);
 }
 
-// Workspace up to which larger blocks are taken than those of least memory.
+// Workspace up to which larger blocks are taken than those of least memory
+// (what sigk_pair_backward_workspace_size asks for; a call given less takes the
+// largest blocks that fit it).
 // With k x k blocks the launches run 2k - 1 anti-diagonals one after another,
 // each a dependency chain of a block's columns and strips: about 5 sweeps of
 // the pair for many blocks, 2.5 for one (and one block needs no first sweep
@@ -1512,11 +1514,11 @@ int long_layout_of(int64_t lx, int64_t ly, int64_t d, int64_t brows, int64_t bco
     return SIGK_OK;
 }
 
-// The layout of a call: the given blocks, or where neither side is given the
-// largest square ones (k x k, k = 1, 2, ...) within kLongRoomy bytes, down to
-// those of least memory.
+// The layout of a call within `room` bytes of workspace: the given blocks, or
+// where neither side is given the largest square ones (k x k, k = 1, 2, ...)
+// that fit it and kLongRoomy, else those of least memory.
 int long_layout(int64_t lx, int64_t ly, int64_t d, int64_t brows, int64_t bcols,
-                const sigk_opts& op, LongLayout& L) {
+                const sigk_opts& op, size_t room, LongLayout& L) {
     int rc = long_layout_of(lx, ly, d, brows, bcols, op, L);
     if (rc || brows || bcols) return rc;
     const int64_t side = std::max(L.m, L.n);
@@ -1524,7 +1526,8 @@ int long_layout(int64_t lx, int64_t ly, int64_t d, int64_t brows, int64_t bcols,
         const int64_t b = ((side + k - 1) / k + kWave - 1) / kWave * kWave;
         if (b <= L.rb && b <= L.cb) break;
         LongLayout T;
-        if (long_layout_of(lx, ly, d, b, b, op, T) == SIGK_OK && T.total <= kLongRoomy) {
+        if (long_layout_of(lx, ly, d, b, b, op, T) == SIGK_OK &&
+            T.total <= std::min(room, kLongRoomy)) {
             L = T;
             break;
         }
@@ -1575,7 +1578,7 @@ int sigk_pair_backward_workspace_size(int64_t lx, int64_t ly, int64_t d, int64_t
                                       int64_t block_cols, const sigk_opts* o, size_t* bytes) {
     if (!bytes || !valid_opts(o)) return SIGK_EINVAL;
     LongLayout L;
-    const int rc = long_layout(lx, ly, d, block_rows, block_cols, opts_or_default(o), L);
+    const int rc = long_layout(lx, ly, d, block_rows, block_cols, opts_or_default(o), kLongRoomy, L);
     if (rc) return rc;
     *bytes = L.total;
     return SIGK_OK;
@@ -1586,7 +1589,7 @@ int sigk_pair_backward_blocks(int64_t lx, int64_t ly, int64_t d, int64_t block_r
                               int64_t* cols_out) {
     if (!rows_out || !cols_out || !valid_opts(o)) return SIGK_EINVAL;
     LongLayout L;
-    const int rc = long_layout(lx, ly, d, block_rows, block_cols, opts_or_default(o), L);
+    const int rc = long_layout(lx, ly, d, block_rows, block_cols, opts_or_default(o), kLongRoomy, L);
     if (rc) return rc;
     *rows_out = L.rb;
     *cols_out = L.cb;
@@ -1600,7 +1603,7 @@ int sigk_pair_backward(const double* x, int64_t lx, const double* y, int64_t ly,
     if (!valid_opts(o)) return SIGK_EINVAL;
     const sigk_opts op = opts_or_default(o);
     LongLayout L;
-    int rc = long_layout(lx, ly, d, block_rows, block_cols, op, L);
+    int rc = long_layout(lx, ly, d, block_rows, block_cols, op, ws_bytes, L);
     if (rc) return rc;
     if (!ws || !grad_out || (lx > 0 && (!x || !grad_x)) || (ly > 0 && (!y || !grad_y)))
         return SIGK_EINVAL;

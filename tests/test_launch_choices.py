@@ -43,3 +43,29 @@ def test_first_call_knows_the_device(cus):
         for r in (first, again, last):
             r["events"] = [e for e in r["events"] if e[0] == "launch"]
         assert first == again == last, (cus, job)
+
+
+def least_rows(side):
+    """Side of the least-memory blocks: sqrt(14.2 side), in whole strips."""
+    return max(64, round((14.2 * side) ** 0.5 / 64) * 64)
+
+
+@pytest.mark.parametrize("order,d,longer,shorter", [(5, 8, 28001, 27001), (8, 8, 22001, 21001),
+                                                    (12, 8, 18001, 17001), (10, 16, 20001, 3000)])
+def test_pair_backward_takes_the_workspace_it_is_given(order, d, longer, shorter):
+    """A workspace sized for a longer pair serves a shorter one, the least-memory
+    blocks' bytes serve a call without block sizes (by blocks no smaller than
+    those), and far less is refused before anything is launched."""
+    q = dict(call="pair_backward", order=order, d=d)
+    sized, = record([dict(q, lx=longer, ly=longer, ws=0)])
+    rows = least_rows(shorter - 1)
+    least, = record([dict(q, lx=shorter, ly=shorter, rows=rows, ws=0)])
+    assert least["rc"] == sized["rc"] == 0 and least["bytes"] < sized["bytes"]
+    s = dict(q, lx=shorter, ly=shorter)
+    fits, tight, explicit, none = record([dict(s, ws=sized["bytes"]), dict(s, ws=least["bytes"]),
+                                          dict(s, ws=least["bytes"], rows=rows),
+                                          dict(s, ws=least["bytes"] // 2)])
+    assert fits["rc"] == tight["rc"] == explicit["rc"] == 0
+    # larger blocks are fewer launches
+    assert len(fits["events"]) < len(tight["events"]) <= len(explicit["events"])
+    assert none["rc"] == -2 and none["events"] == []
