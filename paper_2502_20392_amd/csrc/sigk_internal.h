@@ -98,10 +98,6 @@ __host__ __device__ constexpr int alt_chunk_cols(int P, int D) {
     return fwd_chunk_cols(P, D) == 64 ? 32 : 64;
 }
 
-// Pairs up to which the forward launch's last workgroup checks the truncation
-// estimates itself (beyond, a kernel of its own has more threads for it).
-constexpr int64_t kFusedCheckPairs = 4096;
-
 // Per-pair geometry for table mode (ragged batches).  Offsets in elements.
 struct PairDesc {
     int64_t x_off;      // first double of path x in the pool

@@ -69,3 +69,20 @@ def test_pair_backward_takes_the_workspace_it_is_given(order, d, longer, shorter
     # larger blocks are fewer launches
     assert len(fits["events"]) < len(tight["events"]) <= len(explicit["events"])
     assert none["rc"] == -2 and none["events"] == []
+
+
+def test_truncation_check_is_fused_in_small_launches_only():
+    """The last workgroup checks the estimates where few count themselves; larger
+    launches, and few workgroups over many pairs, leave it to a kernel of its own."""
+    small = [dict(call="gram", nx=n, lx=20, d=3, order=8) for n in (2, 8, 15)]
+    small += [dict(call="plan", lens=[300] * 21, pairs=[[i, i + 1] for i in range(20)], d=3,
+                   order=10, steps=["run"])]
+    large = [dict(call="gram", nx=n, lx=20, d=d, order=p)
+             for n, d, p in ((24, 32, 4), (64, 3, 8), (64, 16, 10), (90, 8, 6))]
+    large += [dict(call="gram", nx=64, lx=20, d=3, order=8, grid=16),
+              dict(call="gram", nx=24, lx=256, d=3, order=6),
+              dict(call="plan", lens=[60] * 301, pairs=[[i, i + 1] for i in range(300)], d=3,
+                   order=10, steps=["run"])]
+    res = record(small + large)
+    assert all("finalize_kernel" not in kernels(r) for r in res[:len(small)])
+    assert all("finalize_kernel" in kernels(r) for r in res[len(small):])
