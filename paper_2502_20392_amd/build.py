@@ -95,6 +95,9 @@ def build(force: bool = False, jobs: int = 0, verbose: bool = False) -> str:
     for p, d in _variants("SIGK_FWD_VARIANTS"):
         units.append(("sigk_fwd.hip", f"fwdt_{p}_{d}.o",
                       [("SIGK_P", p), ("SIGK_D", d), ("SIGK_ALT", 1)]))
+    for p, d in _variants("SIGK_FWDL_VARIANTS"):
+        units.append(("sigk_fwd.hip", f"fwdl_{p}_{d}.o",
+                      [("SIGK_P", p), ("SIGK_D", d), ("SIGK_LONE", 1)]))
     for p, d in _variants("SIGK_FWDG_VARIANTS"):
         units.append(("sigk_fwd.hip", f"fwd_{p}_{d}.o", [("SIGK_P", p), ("SIGK_D", d)]))
     for p, d in _variants("SIGK_FWDSQ_VARIANTS"):

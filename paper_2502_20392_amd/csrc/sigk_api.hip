@@ -53,6 +53,10 @@ const Variant kFwdSqTable[] = {SIGK_FWDSQ_VARIANTS(SIGK_V_FWDSQ)};
 const Variant kFwdGTable[] = {SIGK_FWDG_VARIANTS(SIGK_V_FWDG)};
 #undef SIGK_V_FWDG
 
+#define SIGK_V_FWDL(P, D) {P, D, launch_fwdl_##P##_##D, occupancy_fwdl_##P##_##D, nullptr, nullptr, nullptr, nullptr, nullptr},
+const Variant kFwdLTable[] = {SIGK_FWDL_VARIANTS(SIGK_V_FWDL)};
+#undef SIGK_V_FWDL
+
 struct TeamVariant {
     int P, D;
     hipError_t (*launch)(const FwdArgs&, int, hipStream_t);
@@ -111,6 +115,12 @@ const Variant* find_fwd(int P, int D, uint32_t flags = 0, int tile = 0) {
         if (v.P == P && v.D == D) return &v;
     return nullptr;
 }
+// The 64-column tile compiled for one wave per SIMD, where there is one.
+const Variant* find_lone(int P, int D) {
+    for (const Variant& v : kFwdLTable)
+        if (v.P == P && v.D == D) return &v;
+    return nullptr;
+}
 const TeamVariant* find_team(int P, int D) {
     for (const TeamVariant& v : kTeamTable)
         if (v.P == P && v.D == D) return &v;
@@ -140,6 +150,7 @@ enum {
     kKernelFwdSq = 3,
     kKernelLines = 4,
     kKernelFwdT = 5,  // forward with the alternative work tile
+    kKernelFwdL = 6,  // forward, 64 columns, one wave per SIMD
     kKernelTeam = 16  // + compute waves per team
 };
 
@@ -179,6 +190,9 @@ int device_wgs(int P, int D, int kind) {
         const Variant* v = find_fwd(P, D, kind == kKernelFwdSq ? SIGK_FLAG_SQUARE : 0,
                                     kind == kKernelFwdT ? alt_chunk_cols(P, D) : 0);
         occ = v ? v->occ_fwd() : 0;
+    } else if (kind == kKernelFwdL) {
+        const Variant* v = find_lone(P, D);
+        occ = v ? v->occ_fwd() : 0;
     } else {
         const Variant* v = find_bwd(P, D);
         occ = v ? (kind == kKernelBwd    ? v->occ_bwd()
@@ -192,17 +206,62 @@ int device_wgs(int P, int D, int kind) {
     return value;
 }
 
-// Whether a launch of a variant whose default tile runs two waves per SIMD takes
-// its 32-column tile, which runs one (lone_narrow): where the longest chain of
-// strips outweighs the work over one wave per SIMD, a second wave only slows the
-// chain.  chain and work in steps, the chain with the default tile's lag.  Default
-// tile over this one, order 10, d 16, work over chain 0.4-1.06: 1.14-1.33; 1.21-1.42:
-// 0.92-0.98; 2.3: 0.86 (order 12, d 8: 1.17-1.38, 0.96-1.02, 0.91).
-constexpr double kLoneRatio = 1.1;
-bool lone_tile(int P, int D, const sigk_opts& op, double chain, double work) {
-    return lone_narrow(P, D) && op.tile_cols == 0 && op.grid <= 0 &&
-           !(op.flags & SIGK_FLAG_SQUARE) && kLoneRatio * chain > work / (4.0 * device_cus());
+// Kernel and workgroups of a forward launch of one wave per workgroup.
+struct FwdPick {
+    const Variant* v;
+    int wgs;
+    int cols;  // of its tile
+};
+// Its rule.  chain: steps of the launch's longest chain of strips, with the
+// default tile's lag; work: steps of all its strips.  Where no tile or grid is
+// asked for and the default is 64 columns, the 32-column tile (a start lag of 95
+// steps instead of 127, the same values) is taken if the chain outweighs the
+// work: 1.03-1.23 times as fast on 20-512 pairs of 16-900 points at orders 10-12;
+// 6-9% slower on batches that fill the chip.  Variants of two waves per SIMD
+// (has_lone) run one per SIMD until the work, over one wave per SIMD, is clearly
+// more than the chain, also on a tile or grid that was asked for.  Time of the
+// kernel before the two-wave form over two waves / one / the 32-column tile, lists
+// of 60-1200 pairs of 100-2048 points by work over chain:
+//   order 10, d 16: 0.44 0.83 / 0.99 / 1.10, 0.77 0.73 / 0.99 / 0.94, 1.02 0.81 / 0.99 /
+//     0.95, 1.25 0.95 / 1.00 / 0.93, 1.61 1.02 / 1.00 / 0.93, 2.06 1.15 / 1.02 / 0.98
+//   order 10, d 3: 0.45 0.96 / 1.03 / 1.12, 0.77 0.80 / 1.03 / 0.99, 1.17 0.94 / 1.02 /
+//     0.95, 1.53 1.03 / 1.05 / 0.99, 1.80 1.12 / 1.00 / 0.96, 2.75 1.13 / 1.02 / 0.95
+//   order 12, d 8: 0.57 0.79 / 1.02 / 1.10, 1.01 0.83 / 1.02 / 1.01, 1.45 0.95 / 1.04 /
+//     1.00, 1.99 1.09 / 1.05 / 0.97
+// and the 32-column tile at order 10, d 3, where two waves of it fit a SIMD, held to
+// one / free: 0.46 1.11 / 0.96, 0.92 0.98 / 0.91, 1.07 1.02 / 0.94, 1.29 0.97 / 1.11.
+constexpr double kNarrowWork = 0.65, kCapWork = 1.1, kLoneWork = 1.55;
+FwdPick pick_fwd(int P, int D, const sigk_opts& op, double chain, double work) {
+    const bool square = (op.flags & SIGK_FLAG_SQUARE) != 0;
+    const bool open = op.tile_cols == 0 && op.grid <= 0 && !square;
+    const int simds = 4 * device_cus();
+    int tile = op.tile_cols;
+    if (D > 0 && !square && has_lone(P, D)) {
+        const double w = work / simds;
+        if (open && lone_narrow(P, D) && w < kNarrowWork * chain) tile = 32;
+        const Variant* lone = chunk_of(P, D, tile) == 64 ? find_lone(P, D) : nullptr;
+        if (lone && (w < kLoneWork * chain || (op.grid > 0 && op.grid <= simds)))
+            return {lone, op.grid > 0 ? op.grid : std::min(device_wgs(P, D, kKernelFwdL), simds), 64};
+        // (its registers may let a second wave onto the SIMDs)
+        if (chunk_of(P, D, tile) == 32 && lone_narrow(P, D) && op.grid <= 0 && w < kCapWork * chain)
+            return {find_fwd(P, D, op.flags, tile),
+                    std::min(device_wgs(P, D, fwd_kind(P, D, op.flags, tile)), simds), 32};
+    } else if (open && D > 0 && fwd_chunk_cols(P, D) == 64 &&
+               chain > 1.5 * work / std::max(device_wgs(P, D, kKernelFwd), 1)) {
+        tile = 32;
+    }
+    return {find_fwd(P, D, op.flags, tile),
+            op.grid > 0 ? op.grid : device_wgs(P, D, fwd_kind(P, D, op.flags, tile)),
+            chunk_of(P, D, tile)};
 }
+// The same for a Gram call.
+FwdPick pick_gram(int P, int D, const sigk_opts& op, int64_t strips, int64_t npairs, int64_t m) {
+    const double sweep = (double)(m + kWave - 1);
+    return pick_fwd(P, D, op,
+                    sweep + (double)(strips - 1) * (fwd_chunk_cols(P, D) + kWave - 1),
+                    sweep * (double)(strips * npairs));
+}
+
 // Whether the last workgroup of a forward launch checks the truncation estimates
 // itself, which saves the check's launch but has every workgroup count itself at
 // one address (about 10 ns each, one after another).  Fused less separate, Gram
@@ -211,22 +270,6 @@ bool lone_tile(int P, int D, const sigk_opts& op, double chain, double work) {
 constexpr int64_t kFusedCheckGroups = 128, kFusedCheckPairs = 512;
 bool fused_check(int64_t groups, int64_t npairs) {
     return groups <= kFusedCheckGroups && npairs <= kFusedCheckPairs;
-}
-
-// Workgroups of a launch on the tile taken here: where its registers would let a
-// second wave onto the SIMDs (order 10, d <= 8), no more than one per SIMD
-// (136 pairs of 1024 points: 2.37 ms with two, 2.04 with one).
-int tile_wgs(int P, int D, const sigk_opts& op, int tile) {
-    const int g = device_wgs(P, D, fwd_kind(P, D, op.flags, tile));
-    return tile != op.tile_cols && lone_narrow(P, D) ? std::min(g, 4 * device_cus()) : g;
-}
-// The same for a Gram call: the tile its one-wave kernel takes.
-int gram_tile(int P, int D, const sigk_opts& op, int64_t strips, int64_t npairs, int64_t m) {
-    const double sweep = (double)(m + kWave - 1);
-    return lone_tile(P, D, op, sweep + (double)(strips - 1) * (64 + kWave - 1),
-                     sweep * (double)(strips * npairs))
-               ? 32
-               : op.tile_cols;
 }
 
 // Compute waves per team of a Gram call's forward sweep (the team kernel), 0
@@ -251,8 +294,8 @@ int team_waves(int P, int D, const sigk_opts& op, int64_t strips, int64_t npairs
     // a step of one of w waves on a SIMD against a lone wave's (5.25, 7.1 and
     // 9.1 cycles per FP64 instruction measured for 1, 2 and 3)
     auto slow = [](double w) { return 1.0 + 0.37 * std::max(0.0, w - 1.0); };
-    const bool lone = gram_tile(P, D, op, strips, npairs, m) == 32;
-    const double cap1 = tile_wgs(P, D, op, lone ? 32 : 0);
+    const FwdPick one = pick_gram(P, D, op, strips, npairs, m);
+    const double cap1 = std::max(one.wgs, 1);
     const double all1 = (double)(npairs * strips);
     const double cap_t = device_wgs(P, D, kKernelTeam + W), all_t = (double)(npairs * groups);
     const double f1 = slow(std::min(all1, cap1) / simds);
@@ -260,7 +303,7 @@ int team_waves(int P, int D, const sigk_opts& op, int64_t strips, int64_t npairs
     // the one-wave kernel's chunk round trips, against its steps
     const double trips = P <= 8 ? 1.15 : P <= 12 ? 1.1 : 1.03;
     const double chain1 =
-        trips * (sweep + (double)(strips - 1) * ((lone ? 32 : fwd_chunk_cols(P, D)) + kWave - 1));
+        trips * (sweep + (double)(strips - 1) * (one.cols + kWave - 1));
     const double chain_t = sweep + (double)(strips - 1) * lag;
     const double t1 = std::max(chain1 * (all1 <= cap1 ? f1 : 1.0), sweep * all1 / cap1 * f1);
     const double t_t = std::max(chain_t * (all_t <= cap_t ? f_t : 1.0),
@@ -532,22 +575,6 @@ hipError_t plan_reset(const sigk_plan* plan, double* out, char* base, hipStream_
     return e;
 }
 
-// Work tile of a plan's forward sweep.  Where none is asked for and the default
-// is 64 columns, the 32-column tile (a start lag of 95 steps instead of 127, the
-// same values) is taken if the longest chain of strips outweighs the work over
-// the resident waves.  Default over 32 columns, measured on 20-512 pairs of
-// 16-900 points: 1.03-1.23 at orders 10-12; the other way round by 6-9% on
-// batches that fill the chip (Gram, order 10-12).
-int plan_tile(const sigk_plan& p) {
-    if (p.opts.tile_cols != 0 || p.opts.grid > 0 || (p.opts.flags & SIGK_FLAG_SQUARE) ||
-        fwd_chunk_cols(p.P, p.D) != 64)
-        return p.opts.tile_cols;
-    if (lone_narrow(p.P, p.D))
-        return lone_tile(p.P, p.D, p.opts, (double)p.chain, (double)p.work) ? 32 : 0;
-    const double work = (double)p.work / (double)std::max(device_wgs(p.P, p.D, kKernelFwd), 1);
-    return (double)p.chain > 1.5 * work ? 32 : 0;
-}
-
 // The forward sweep of a plan (after plan_reset): one persistent launch, then
 // the truncation-estimate check.
 int fwd_pass(const sigk_plan* plan, const double* pool, double* out, char* base, hipStream_t s) {
@@ -570,15 +597,12 @@ int fwd_pass(const sigk_plan* plan, const double* pool, double* out, char* base,
     a.hdr = hdr;
     a.trunc_est = est;
     a.budget = budget_of(plan->opts);
-    const int tile = plan_tile(*plan);
-    const Variant* v = find_fwd(plan->P, plan->D, plan->opts.flags, tile);
-    if (!v) return SIGK_EUNSUPPORTED;
-    int grid = plan->opts.grid > 0
-                   ? plan->opts.grid
-                   : tile_wgs(plan->P, plan->D, plan->opts, tile);
-    grid = (int)std::max<int64_t>(std::min<int64_t>(grid, a.ntickets), 1);
+    const FwdPick one =
+        pick_fwd(plan->P, plan->D, plan->opts, (double)plan->chain, (double)plan->work);
+    if (!one.v) return SIGK_EUNSUPPORTED;
+    const int grid = (int)std::max<int64_t>(std::min<int64_t>(one.wgs, a.ntickets), 1);
     a.check = fused_check(grid, plan->npairs);
-    hipError_t e = v->fwd(a, grid, s);
+    hipError_t e = one.v->fwd(a, grid, s);
     if (e == hipSuccess && !a.check)
         e = launch_finalize(hdr, est, plan->npairs, budget_of(plan->opts), s);
     if (e != hipSuccess) return device_error(e);
@@ -715,13 +739,11 @@ int sigk_gram(const double* X, int64_t nx, const double* Y, int64_t ny, int64_t 
         a.check = fused_check(grid, L.npairs);
         e = find_team(P, D)->launch(a, grid, s);
     } else {
-        const int tile = gram_tile(P, D, op, L.strips, L.npairs, lx - 1);
-        if (tile != op.tile_cols) v = find_fwd(P, D, op.flags, tile);
-        if (!v) return SIGK_EUNSUPPORTED;
-        int grid = op.grid > 0 ? op.grid : tile_wgs(P, D, op, tile);
-        grid = (int)std::max<int64_t>(std::min<int64_t>(grid, a.ntickets), 1);
+        const FwdPick one = pick_gram(P, D, op, L.strips, L.npairs, lx - 1);
+        if (!one.v) return SIGK_EUNSUPPORTED;
+        const int grid = (int)std::max<int64_t>(std::min<int64_t>(one.wgs, a.ntickets), 1);
         a.check = fused_check(grid, L.npairs);
-        e = v->fwd(a, grid, s);
+        e = one.v->fwd(a, grid, s);
     }
     if (e == hipSuccess && !a.check)
         e = launch_finalize(hdr, est, L.npairs, budget_of(op), s);

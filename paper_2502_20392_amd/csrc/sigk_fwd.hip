@@ -12,7 +12,8 @@
 // tile matrix, selected by SIGK_FLAG_SQUARE) under the launcher names
 // launch_fwdsq_P_D / occupancy_fwdsq_P_D; -DSIGK_ALT=1 the variant with the
 // other frontier chunk width (alt_chunk_cols) as launch_fwdt_P_D /
-// occupancy_fwdt_P_D.
+// occupancy_fwdt_P_D; -DSIGK_LONE=1 the 64-column tile for one wave per SIMD
+// (SIGK_FWDL_VARIANTS) as launch_fwdl_P_D / occupancy_fwdl_P_D.
 #include "sigk_strip.h"
 #include "sigk_team.h"
 
@@ -28,18 +29,24 @@
 #ifndef SIGK_ALT
 #define SIGK_ALT 0
 #endif
+#ifndef SIGK_LONE
+#define SIGK_LONE 0
+#endif
 
 namespace sigk {
 
-template <int P, int D, bool SQ, int CH>
-__global__ void __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(fwd_tile_waves(P, D, CH)))) fwd_kernel(FwdArgs a) {
+template <int P, int D, bool SQ, int CH, bool LONE = false>
+__global__ void __launch_bounds__(kWave)
+    __attribute__((amdgpu_waves_per_eu(LONE ? 1 : fwd_tile_waves(P, D, CH)))) fwd_kernel(FwdArgs a) {
     // Two waves per SIMD share the CU's LDS with eight waves: a narrower ring
     // at order 10 where d > 8, the frontier written 32 columns at a time.
-    constexpr bool kTwo = fwd_tile_waves(P, D, CH) == 2;
+    constexpr bool kTwo = !LONE && fwd_tile_waves(P, D, CH) == 2;
     // The 32-column tile of a variant whose default is 64 keeps that one's ring
-    // and depths: launches may take either and give the same values.
+    // and depths, and the form of one wave per SIMD its depths: launches may
+    // take any of them and give the same values.
     constexpr bool kNarrow = CH == 32 && D > 0 && fwd_chunk_cols(P, D) == 64;
-    constexpr int RB = CH == 64 || kNarrow ? chunk64_ring(P, D) : ring_cols(P);
+    constexpr int INC = kNarrow || LONE ? inc_chunk<64, chunk64_ring(P, D)> : 0;
+    constexpr int RB = LONE ? 128 : CH == 64 || kNarrow ? chunk64_ring(P, D) : ring_cols(P);
     constexpr int TC = kTwo ? 32 : CH;
     __shared__ LdsStrip<P, D, CH, RB, TC> L;
     Acc acc;
@@ -62,7 +69,7 @@ __global__ void __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(fwd_
             if (pair < 0) break;  // unused slots close a table built on the device
         }
         Geo g = resolve(a, pair, P, 0);
-        StripCtx<P, D, CH, RB, SQ, false, TC, kNarrow> S(a, g, L, acc, strip);
+        StripCtx<P, D, CH, RB, SQ, false, TC, INC, (P <= 8 || LONE)> S(a, g, L, acc, strip);
         S.pair = pair;
         S.Fout = a.frontier + g.front;
         S.Fin = S.Fout;
@@ -78,7 +85,10 @@ __global__ void __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(fwd_
 #define SIGK_CAT3(a, b, c) a##b##_##c
 #define SIGK_NAME(pre, P, D) SIGK_CAT3(pre, P, D)
 
-#if SIGK_SQ
+#if SIGK_LONE
+#define SIGK_LAUNCH launch_fwdl_
+#define SIGK_OCC occupancy_fwdl_
+#elif SIGK_SQ
 #define SIGK_LAUNCH launch_fwdsq_
 #define SIGK_OCC occupancy_fwdsq_
 #elif SIGK_ALT
@@ -88,10 +98,12 @@ __global__ void __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(fwd_
 #define SIGK_LAUNCH launch_fwd_
 #define SIGK_OCC occupancy_fwd_
 #endif
-constexpr int kChunk = SIGK_ALT ? alt_chunk_cols(SIGK_P, SIGK_D) : fwd_chunk_cols(SIGK_P, SIGK_D);
+constexpr int kChunk = SIGK_LONE  ? 64
+                       : SIGK_ALT ? alt_chunk_cols(SIGK_P, SIGK_D)
+                                  : fwd_chunk_cols(SIGK_P, SIGK_D);
 
 hipError_t SIGK_NAME(SIGK_LAUNCH, SIGK_P, SIGK_D)(const FwdArgs& a, int grid, hipStream_t s) {
-    hipLaunchKernelGGL((fwd_kernel<SIGK_P, SIGK_D, SIGK_SQ != 0, kChunk>), dim3(grid),
+    hipLaunchKernelGGL((fwd_kernel<SIGK_P, SIGK_D, SIGK_SQ != 0, kChunk, SIGK_LONE != 0>), dim3(grid),
                        dim3(kWave), 0, s, a);
     return hipGetLastError();
 }
@@ -99,12 +111,12 @@ hipError_t SIGK_NAME(SIGK_LAUNCH, SIGK_P, SIGK_D)(const FwdArgs& a, int grid, hi
 int SIGK_NAME(SIGK_OCC, SIGK_P, SIGK_D)() {
     int nb = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-            &nb, fwd_kernel<SIGK_P, SIGK_D, SIGK_SQ != 0, kChunk>, kWave, 0) != hipSuccess)
+            &nb, fwd_kernel<SIGK_P, SIGK_D, SIGK_SQ != 0, kChunk, SIGK_LONE != 0>, kWave, 0) != hipSuccess)
         return 0;
     return nb;
 }
 
-#if !SIGK_SQ && !SIGK_ALT
+#if !SIGK_SQ && !SIGK_ALT && !SIGK_LONE
 hipError_t SIGK_NAME(launch_team_, SIGK_P, SIGK_D)(const FwdArgs& a, int grid, hipStream_t s) {
     hipLaunchKernelGGL((team_kernel<SIGK_P, SIGK_D>), dim3(grid), dim3(kWave * (a.team + 1)),
                        (team_lds_bytes<SIGK_P, SIGK_D>(a.team)), s, a);

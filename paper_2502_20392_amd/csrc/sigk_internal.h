@@ -79,14 +79,27 @@ __host__ __device__ constexpr int chunk64_ring(int P, int D) {
 __host__ __device__ constexpr int fwd_waves(int P, int D) {
     return P <= 6 && D <= 8 ? 3 : (P >= 8 && D > 0 && (P <= 10 ? D <= 16 : P == 12 && D <= 8) ? 2 : 1);
 }
-// The 32-column tile of a variant whose 64-column default runs two waves per
-// SIMD is compiled for one: launches bound by their chains of strips take it
-// (lone_tile in sigk_api.hip), and there a second wave on the SIMD makes every
-// step of the chain a third longer (136 pairs of 1024 points, order 10, d 16:
-// 2.14 ms with one wave per SIMD, 2.68 with two).
-__host__ __device__ constexpr bool lone_narrow(int P, int D) {
-    return P >= 8 && D > 0 && fwd_waves(P, D) == 2 && fwd_chunk_cols(P, D) == 64;
+// Variants of two waves per SIMD whose 64-column tile (the default or the other
+// one) is also compiled for one wave per SIMD (launch_fwdl_P_D): where the
+// dependency chain of a launch is about as long as its work or longer, a second
+// wave on the SIMD only makes every step of the chain a third longer.  Gram
+// matrix of 22 paths of 1024 points, order 10, d 16: 3.31 ms with two waves per
+// SIMD, 3.12 with one; of 16 paths 2.88 and 2.14; of 64 paths 18.9 and 23.3.
+#define SIGK_FWDL_VARIANTS(X) X(8, 16) X(10, 8) X(12, 8) X(10, 16)
+#define SIGK_HAS_LONE(P_, D_) || (P == P_ && D == D_)
+__host__ __device__ constexpr bool has_lone(int P, int D) {
+    return false SIGK_FWDL_VARIANTS(SIGK_HAS_LONE);
 }
+#undef SIGK_HAS_LONE
+// Of these, the ones whose default tile has 64 columns: their 32-column tile is
+// compiled for one wave per SIMD only (a start lag of 95 steps instead of 127:
+// launches that are far from filling the chip take it).
+__host__ __device__ constexpr bool lone_narrow(int P, int D) {
+    return has_lone(P, D) && fwd_chunk_cols(P, D) == 64;
+}
+static_assert(lone_narrow(10, 8) && lone_narrow(10, 16) && lone_narrow(12, 8) &&
+                  !lone_narrow(8, 16) && !lone_narrow(8, 8) && !lone_narrow(12, 16),
+              "every 64-column default of two waves per SIMD has a form of one");
 __host__ __device__ constexpr int fwd_tile_waves(int P, int D, int CH) {
     return CH == 32 && lone_narrow(P, D) ? 1 : fwd_waves(P, D);
 }
@@ -246,6 +259,11 @@ SIGK_FWDG_VARIANTS(SIGK_DECL_FWD)
     int occupancy_fwdt_##P##_##D();
 SIGK_FWD_VARIANTS(SIGK_DECL_FWDT)
 #undef SIGK_DECL_FWDT
+#define SIGK_DECL_FWDL(P, D) \
+    hipError_t launch_fwdl_##P##_##D(const FwdArgs& a, int grid, hipStream_t s); \
+    int occupancy_fwdl_##P##_##D();
+SIGK_FWDL_VARIANTS(SIGK_DECL_FWDL)
+#undef SIGK_DECL_FWDL
 #define SIGK_DECL_FWDSQ(P, D) \
     hipError_t launch_fwdsq_##P##_##D(const FwdArgs& a, int grid, hipStream_t s); \
     int occupancy_fwdsq_##P##_##D();

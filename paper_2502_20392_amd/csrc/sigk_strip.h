@@ -86,10 +86,9 @@ struct RingPos {
 // D > 0: the channel bucket (d <= D, increments in LDS and registers);
 // D = 0: the cell coefficients come from a field computed beforehand.
 // Columns per increment load and Neumann depth: 64 where a 128-column ring
-// serves 64-column chunks, or 32-column ones that must give the same depths
-// (wide), else 32.
-template <int CH, int RB, bool wide = false>
-constexpr int inc_chunk = RB >= 64 + kWave - 1 && (CH == 64 || wide) ? 64 : 32;
+// serves 64-column chunks, else 32.
+template <int CH, int RB>
+constexpr int inc_chunk = RB >= 64 + kWave - 1 && CH == 64 ? 64 : 32;
 
 template <int P, int D, int CH, int RB, int TC = CH>
 struct LdsStrip {
@@ -429,11 +428,14 @@ __device__ __forceinline__ void lds_copy(double* dst, const double* src) {
 // square truncation of the tile matrix (the paper's fixed-order tile); BLK:
 // the boundary hooks of block checkpointing (left edges from a line, a bottom
 // line for strip 0, right-edge lines written during the sweep).
-// TC: columns staged per frontier write.
+// TC: columns staged per frontier write.  INC: columns per increment load and
+// depth where not those of the chunk and ring (a tile that gives another's values).
+// AHEAD: the cell coefficient is formed a step ahead.
 template <int P, int D, int CH, int RB, bool SQ = false, bool BLK = false, int TC = CH,
-          bool WIDE = false>
+          int INC = 0, bool AHEAD = P <= 8>
 struct StripCtx {
-    static constexpr int XC = D > 0 ? inc_chunk<CH, RB, WIDE> : CH;
+    static constexpr int XC = D == 0 ? CH : INC > 0 ? INC : inc_chunk<CH, RB>;
+    static_assert(D == 0 || RB >= XC + kWave - 1, "the ring holds a load and the 63 columns before");
     static constexpr int EV = XC < CH ? XC : CH;  // steps between two loads
     const FwdArgs& a;
     Geo& g;
@@ -682,10 +684,12 @@ struct StripCtx {
     // Cell coefficient c = <dx_col, dy_row> of step t into cn.  For small
     // orders it is computed one step ahead so that the LDS latency of the
     // increments overlaps the cell map (several waves share a SIMD there and
-    // registers allow it).  Every ring slot read is inside the LDS array for
+    // registers allow it), and in the form of orders 10-12 for one wave per
+    // SIMD, which has the registers and no other wave to cover the reads (order
+    // 10, d 16: 1-2% of the time).  Every ring slot read is inside the LDS array for
     // any t; where step t starts a new chunk the value read ahead is stale and
     // is recomputed after load_chunk().
-    static constexpr bool kAhead = P <= 8;
+    static constexpr bool kAhead = AHEAD;
     RingPos<RB> rp;  // (not kAhead) the slot of the step's column, stepped
     __device__ __forceinline__ void prefetch(int t) {
         if constexpr (D == 0) {

@@ -63,15 +63,17 @@ int hipFuncSetAttribute(const void* f, int, int value) {
     g_events.push_back({"attribute", name_of(f), 0, 0, value});
     return 0;
 }
-int hipOccupancyMaxActiveBlocksPerMultiprocessor(int* n, const void* f, int, size_t) {
+int hipOccupancyMaxActiveBlocksPerMultiprocessor(int* n, const void* f, int block, size_t lds) {
     const std::string name = name_of(f);
-    *n = 4;
+    *n = 4;  // waves per CU
     size_t best = 0;
     for (auto& o : g_occ)
         if (o.first.size() > best && name.find(o.first) != std::string::npos) {
             best = o.first.size();
             *n = o.second;
         }
+    *n /= block / 64;
+    if (lds > 0 && *n > (int)(163840 / lds)) *n = (int)(163840 / lds);
     return 0;
 }
 int hipGetDevice(int* d) {

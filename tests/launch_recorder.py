@@ -18,14 +18,20 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 SONAME = "libamdhip64.so.7"
 
-# Workgroups per CU the kernels reach on an MI355X (the mangled template
-# arguments; the longest match counts, 4 = one wave per SIMD otherwise)
+# Waves per CU the kernels reach on an MI355X (part of the mangled name; the
+# longest match counts, 4 = one wave per SIMD otherwise)
 OCCUPANCY = {"10fwd_kernelILi4ELi8E": 12, "10fwd_kernelILi4ELi16E": 8,
              "10fwd_kernelILi5ELi8E": 11, "10fwd_kernelILi5ELi16E": 8,
              "10fwd_kernelILi6ELi8E": 12, "10fwd_kernelILi6ELi16E": 8,
              "10fwd_kernelILi8ELi8E": 8, "10fwd_kernelILi8ELi16E": 7,
              "10fwd_kernelILi10ELi8E": 8, "10fwd_kernelILi10ELi16ELb0ELi64E": 8,
-             "10fwd_kernelILi12ELi8ELb0ELi64E": 8, "11team_kernel": 2}
+             "10fwd_kernelILi12ELi8ELb0ELi64E": 8,
+             **{f"11team_kernelILi{p}ELi{d}E": 12 for p in (4, 5, 6) for d in (0, 8)},
+             **{f"11team_kernelILi{p}ELi16E": 8 for p in (4, 5, 6, 8, 10)},
+             **{f"11team_kernelILi{p}ELi{d}E": 8 for p in (8, 10) for d in (0, 8)},
+             # (their forms of one wave per SIMD)
+             "10fwd_kernelILi8ELi16ELb0ELi64ELb1E": 4, "10fwd_kernelILi10ELi8ELb0ELi64ELb1E": 5,
+             "10fwd_kernelILi10ELi16ELb0ELi64ELb1E": 4, "10fwd_kernelILi12ELi8ELb0ELi64ELb1E": 4}
 
 
 def record(jobs):

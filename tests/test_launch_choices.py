@@ -86,3 +86,46 @@ def test_truncation_check_is_fused_in_small_launches_only():
     res = record(small + large)
     assert all("finalize_kernel" not in kernels(r) for r in res[:len(small)])
     assert all("finalize_kernel" in kernels(r) for r in res[len(small):])
+
+
+def forward(result):
+    """(kernel, workgroups) of the forward sweep."""
+    (e,) = [e for e in result["events"] if e[0] == "launch" and
+            e[1].startswith(("fwd_kernel", "team_kernel"))]
+    return e[1], e[2]
+
+
+def pairs_of(n, length, **kw):
+    return dict(call="plan", lens=[length] * (n + 1), pairs=[[i, i + 1] for i in range(n)],
+                steps=["run"], **kw)
+
+
+@pytest.mark.parametrize("order,d", [(10, 3), (10, 16), (12, 8)])
+def test_one_wave_per_simd_until_the_work_exceeds_the_chain(order, d):
+    """Variants whose 64-column tile runs two waves per SIMD: launches far from
+    filling the chip take the narrow tile, those whose work is about their chain
+    the form of one wave per SIMD, also where the tile or a grid was asked for, as do
+    grids of no more waves; large ones run two waves per SIMD."""
+    D = 8 if d <= 8 else 16
+    narrow, lone, two = (f"fwd_kernel<{order},{D},0,{t}>" for t in ("32,0", "64,1", "64,0"))
+    q = dict(order=order, d=d)
+    res = record([pairs_of(60, 1024, **q), pairs_of(136, 1024, **q), pairs_of(256, 1024, **q),
+                  pairs_of(256, 1024, tile=64, **q), pairs_of(60, 1024, tile=64, **q),
+                  pairs_of(600, 1024, grid=512, **q), pairs_of(600, 1024, **q),
+                  pairs_of(256, 1024, grid=2048, **q), pairs_of(600, 1024, grid=2048, **q),
+                  pairs_of(136, 1024, tile=32, **q),
+                  dict(call="gram", nx=22, lx=1024, **q), dict(call="gram", nx=64, lx=1024, **q)])
+    got = [forward(r) for r in res]
+    assert got == [(narrow, 960), (lone, 1024), (lone, 1024), (lone, 1024), (lone, 960),
+                   (lone, 512), (two, 2048), (lone, 2048), (two, 2048), (narrow, 1024),
+                   (lone, 1024), (two, 2048)], got
+
+
+def test_order_8_wide_tile_in_its_form_of_one_wave_per_simd():
+    """d 9-16 at order 8 has it on the other tile, for those who ask for it."""
+    q = dict(order=8, d=16)
+    got = [forward(r)[0] for r in record([
+        dict(call="gram", nx=16, lx=1024, tile=64, **q), dict(call="gram", nx=64, lx=512, tile=64, **q),
+        pairs_of(136, 1024, **q), pairs_of(136, 1024, tile=32, **q)])]
+    assert got == ["fwd_kernel<8,16,0,64,1>", "fwd_kernel<8,16,0,64,0>", "fwd_kernel<8,16,0,32,0>",
+                   "fwd_kernel<8,16,0,32,0>"], got
