@@ -277,11 +277,15 @@ bool fused_check(int64_t groups, int64_t npairs) {
 // pair (a start lag of 64 + team_sub steps per strip against 63 + chunk) but
 // runs fewer compute waves, so it is taken where the launch's time is that
 // chain: both kernels' times in steps are estimated as the larger of the chain
-// and of the work over the resident waves.  Measured one-wave over team at
-// lengths 100-2000, orders 5-16 and 1-2048 pairs: 1.05-1.49 where this rule
-// takes the team (order 10, length 1000, d 3: 1.38 for 1 pair, 1.34 for 64),
-// 0.4-1.1 where it does not (0.80 for 512).  An explicit grid or tile width
-// asks for the one-wave kernel.
+// and of the work over the resident waves, on a CU that holds the most teams (300
+// pairs of four strips put two teams on some CUs, ten waves on four SIMDs).
+// Symmetric Gram matrices of 1-90 paths of 65-2048 points, orders 4-24, d 3-32:
+// one-wave over team 1.05-1.49 where this rule takes the team (order 10, length
+// 1000, d 3: 1.38 for 1 pair, 1.34 for 64), 0.4-1.3 where it does not (order 10, 512
+// pairs: 0.80; 24 paths of 256 points at order 6, 300 pairs: 0.74; the most, 1.3, is
+// left at orders 4-6 with 36 pairs of 32 strips).  In the mean it is 0.5% slower
+// than the better of the two.  An explicit grid or tile width asks for the
+// one-wave kernel.
 int team_waves(int P, int D, const sigk_opts& op, int64_t strips, int64_t npairs, int64_t m) {
     if (strips < 2 || op.grid > 0 || op.tile_cols != 0 || (op.flags & SIGK_FLAG_SQUARE)) return 0;
     const TeamVariant* v = find_team(P, D);
@@ -299,16 +303,17 @@ int team_waves(int P, int D, const sigk_opts& op, int64_t strips, int64_t npairs
     const double all1 = (double)(npairs * strips);
     const double cap_t = device_wgs(P, D, kKernelTeam + W), all_t = (double)(npairs * groups);
     const double f1 = slow(std::min(all1, cap1) / simds);
-    const double f_t = slow(std::min(all_t, cap_t) * (W + 1) / simds);
+    const double cus = simds / 4.0;
+    const double f_t = slow(std::min(std::ceil(all_t / cus), cap_t / cus) * (W + 1) / 4.0);
     // the one-wave kernel's chunk round trips, against its steps
     const double trips = P <= 8 ? 1.15 : P <= 12 ? 1.1 : 1.03;
     const double chain1 =
         trips * (sweep + (double)(strips - 1) * (one.cols + kWave - 1));
     const double chain_t = sweep + (double)(strips - 1) * lag;
     const double t1 = std::max(chain1 * (all1 <= cap1 ? f1 : 1.0), sweep * all1 / cap1 * f1);
-    const double t_t = std::max(chain_t * (all_t <= cap_t ? f_t : 1.0),
-                                std::ceil(all_t / cap_t) * (sweep + 0.5 * (W - 1) * lag) * f_t);
-    return t_t < 0.95 * t1 ? W : 0;
+    const double t_t =
+        f_t * std::max(chain_t, std::ceil(all_t / cap_t) * (sweep + 0.5 * (W - 1) * lag));
+    return t_t < 0.9 * t1 ? W : 0;
 }
 
 // Per-cell Neumann tolerance.  A dropped term n is bounded by |c|^n/(n!)^2

@@ -129,3 +129,15 @@ def test_order_8_wide_tile_in_its_form_of_one_wave_per_simd():
         pairs_of(136, 1024, **q), pairs_of(136, 1024, tile=32, **q)])]
     assert got == ["fwd_kernel<8,16,0,64,1>", "fwd_kernel<8,16,0,64,0>", "fwd_kernel<8,16,0,32,0>",
                    "fwd_kernel<8,16,0,32,0>"], got
+
+
+def test_teams_only_where_they_are_the_faster_kernel():
+    """Gram calls measured with both kernels: a team's waves must find SIMDs of their
+    own also on the CU that holds the most teams."""
+    one = [(4, 8, 256, 24), (5, 8, 256, 24), (6, 3, 256, 24), (8, 16, 128, 24), (10, 8, 128, 24),
+           (12, 16, 256, 16), (12, 16, 512, 16), (16, 3, 512, 16), (10, 3, 1024, 22)]
+    team = [(6, 8, 4096, 1), (10, 3, 128, 8), (10, 3, 1000, 1), (5, 8, 1024, 8), (12, 32, 300, 4),
+            (16, 8, 1024, 4), (8, 16, 500, 8)]
+    res = record([dict(call="gram", order=p, d=d, lx=n, nx=nx) for p, d, n, nx in one + team])
+    got = [forward(r)[0].startswith("team_kernel") for r in res]
+    assert got == [False] * len(one) + [True] * len(team), list(zip(one + team, got))
