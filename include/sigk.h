@@ -194,10 +194,13 @@ size_t sigk_plan_backward_workspace_size(const sigk_plan* plan);
 /* Number of Goursat cells of the batch (host). */
 uint64_t sigk_plan_cells(const sigk_plan* plan);
 /*
- * Copy the plan's device tables into ws (asynchronous on stream from host
- * memory held by the plan; keep the plan alive until the stream has passed
- * this call).  Needed once per workspace before sigk_plan_run.
+ * Copy the plan's device tables into ws, asynchronous on stream.  Needed once per
+ * workspace before sigk_plan_run.  Tables of up to SIGK_PLAN_ARG_BYTES (64 bytes a
+ * pair and 16 a strip of 64 rows) are taken when the call returns; larger ones are
+ * copied from host memory held by the plan: keep it alive until the stream has
+ * passed this call.
  */
+enum { SIGK_PLAN_ARG_BYTES = 32768 };
 int sigk_plan_upload(const sigk_plan* plan, void* ws, size_t ws_bytes, void* stream);
 /*
  * Output slots (host, before sigk_plan_upload): pair p writes

@@ -27,6 +27,7 @@ FLAG_SQUARE = 2
 FLAG_FIELD = 4
 
 STATIC_WS_BYTES = 64 << 20  # SIGK_STATIC_WS_BYTES
+PLAN_ARG_BYTES = 32768  # SIGK_PLAN_ARG_BYTES
 
 ORDERS = (4, 5, 6, 8, 10, 12, 16, 20, 24)
 BWD_ORDERS = (4, 5, 6, 8, 10, 12, 16, 20, 24)

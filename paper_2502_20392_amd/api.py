@@ -312,7 +312,7 @@ class RaggedPlan:
         launches have taken when it returns): 64 bytes a pair, 16 a strip."""
         n = ctypes.c_int64()
         _lib.check(_lib.load().sigk_plan_tickets(self._h, 0, None, 0, ctypes.byref(n)))
-        return 64 * self.npairs + 16 * n.value <= 32768
+        return 64 * self.npairs + 16 * n.value <= _lib.PLAN_ARG_BYTES
 
     def run(self, pool, out=None):
         """out[p] = k(pairs[p]) for pool [sum len, d]; no host-device copies (capturable

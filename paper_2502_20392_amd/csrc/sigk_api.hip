@@ -917,7 +917,7 @@ __global__ void chain_kernel(const double* gdx, double* gpool, int64_t npts, int
 // it returns, so nothing on the host waits for the stream or outlives the call
 // (a copy from ordinary memory waits for the work before it: a training step
 // on 16 paths of 100 points took 1000 us that way and 759 without).
-constexpr size_t kArgUploadBytes = 32768;  // about nine launches
+constexpr size_t kArgUploadBytes = SIGK_PLAN_ARG_BYTES;  // about nine launches
 struct ArgWords {
     uint64_t w[448];
 };

@@ -1,6 +1,8 @@
 """What the host side launches, recorded without a GPU (launch_recorder.py)."""
 import os
+import re
 
+import numpy as np
 import pytest
 
 from launch_recorder import kernels, record
@@ -141,3 +143,25 @@ def test_teams_only_where_they_are_the_faster_kernel():
     res = record([dict(call="gram", order=p, d=d, lx=n, nx=nx) for p, d, n, nx in one + team])
     got = [forward(r)[0].startswith("team_kernel") for r in res]
     assert got == [False] * len(one) + [True] * len(team), list(zip(one + team, got))
+
+
+def test_small_tables_are_taken_when_the_upload_returns():
+    """Up to the header's limit the upload copies nothing from host memory, which is
+    what lets the autograd calls skip their wait for it; beyond it does.  The
+    limit and the table sizes are the binding's."""
+    from paper_2502_20392_amd import _lib, api
+    text = open(os.path.join(ROOT, "include", "sigk.h")).read()
+    limit = int(re.search(r"SIGK_PLAN_ARG_BYTES = (\d+)", text).group(1))
+    assert _lib.PLAN_ARG_BYTES == limit
+    one, two, none = [0, 0], [0, 1], [0, 2]  # pairs of one, two and no strips
+    lens = [30, 100, 1]
+    n = limit // 80
+    at = [one] * (n - (limit - 80 * n) // 16) + [two] * ((limit - 80 * n) // 16)
+    tables = [at, at + [none], at[:-1] + [none], [one] * (n - 1), [one] * (2 * n)]
+    small = [64 * len(t) + 16 * (t.count(one) + 2 * t.count(two)) <= limit for t in tables]
+    assert small == [True, False, True, True, False]
+    jobs = [dict(call="plan", lens=lens, pairs=t, d=3, order=6, steps=["upload"]) for t in tables]
+    for t, ok, r in zip(tables, small, record(jobs)):
+        assert r["rc"] == 0 and ok == all(e[0] != "copy" for e in r["events"]), (ok, r["events"])
+        plan = api.RaggedPlan(np.cumsum([0] + lens), np.array(t, np.int32), 3, order=6, device="cpu")
+        assert plan._small_tables() == ok
