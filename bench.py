@@ -152,9 +152,10 @@ def extras(torch, sk, dev, only=""):
             tried.append({"order": order, "status": st})
             if not st & _lib.WARN_TRUNC:
                 break
-        # work tile: both compiled chunk widths timed, the faster kept
+        # work tile: the library's own choice (0) and both compiled chunk widths
+        # timed, the fastest kept
         tiles = []
-        for tile in sk.api.tile_options(order, X.shape[2]):
+        for tile in [0] + sk.api.tile_options(order, X.shape[2]):
             tiles.append({"tile": tile, "ms": timed(lambda: sk.gram(X, order=order, tile=tile),
                                                     torch)})
         tile = min(tiles, key=lambda t: t["ms"])["tile"]

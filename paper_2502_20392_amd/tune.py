@@ -81,8 +81,8 @@ def _grid_candidates(order, d):
 
 def tune_ragged(pool, offsets, pairs, hint=6, reps=2, tol=None, use_cache=True):
     """Tune a ragged batch: the edge order (the truncation budget), then the
-    work tile (frontier chunk width, both compiled options) and the persistent
-    grid by timing.  Returns {"order", "tile", "grid", "ms", "status",
+    work tile and the persistent grid by timing: the library's own choice (tile and
+    grid 0), then both compiled chunk widths at a few grids.  Returns {"order", "tile", "grid", "ms", "status",
     "trials"}."""
     d = pool.shape[1]
     key = "ragged:" + _digest(offsets, pairs, pool) + f":{hint}:{tol}"
@@ -102,15 +102,15 @@ def tune_ragged(pool, offsets, pairs, hint=6, reps=2, tol=None, use_cache=True):
         status = st
     best = None
     trials = []
-    for tile in tile_options(order, d):
-        for g in _grid_candidates(order, d):
-            plan = RaggedPlan(offsets, pairs, d, order=order, tol=tol, grid=g, device=pool.device,
-                              tile=tile)
-            out = torch.empty(plan.npairs, dtype=torch.float64, device=pool.device)
-            ms = _time(lambda: plan.run(pool, out), reps)
-            trials.append({"tile": tile, "grid": g, "ms": ms})
-            if best is None or ms < best["ms"]:
-                best = {"order": order, "tile": tile, "grid": g, "ms": ms, "status": status}
+    for tile, g in [(0, 0)] + [(t, g) for t in tile_options(order, d)
+                               for g in _grid_candidates(order, d)]:
+        plan = RaggedPlan(offsets, pairs, d, order=order, tol=tol, grid=g, device=pool.device,
+                          tile=tile)
+        out = torch.empty(plan.npairs, dtype=torch.float64, device=pool.device)
+        ms = _time(lambda: plan.run(pool, out), reps)
+        trials.append({"tile": tile, "grid": g, "ms": ms})
+        if best is None or ms < best["ms"]:
+            best = {"order": order, "tile": tile, "grid": g, "ms": ms, "status": status}
     best["trials"] = trials
     if use_cache:
         _store(key, best)
@@ -120,7 +120,7 @@ def tune_ragged(pool, offsets, pairs, hint=6, reps=2, tol=None, use_cache=True):
 def tune_class_tiles(pool, offsets, pairs, orders, reps=2, tol=None):
     """The work tile of each order class of a per-pair-order batch (see
     tune_ragged_orders), by timing each class's plan with both compiled tile
-    widths.  Returns ({order: tile}, trials)."""
+    widths (a plan's own choice is one of them).  Returns ({order: tile}, trials)."""
     d = pool.shape[1]
     pairs = np.ascontiguousarray(pairs, dtype=np.int32).reshape(-1, 2)
     orders = np.asarray(orders).reshape(-1)
