@@ -165,3 +165,17 @@ def test_small_tables_are_taken_when_the_upload_returns():
         assert r["rc"] == 0 and ok == all(e[0] != "copy" for e in r["events"]), (ok, r["events"])
         plan = api.RaggedPlan(np.cumsum([0] + lens), np.array(t, np.int32), 3, order=6, device="cpu")
         assert plan._small_tables() == ok
+
+
+@pytest.mark.parametrize("order", [5, 8])
+def test_benchmark_warms_every_kernel_of_the_long_gradient(order):
+    import bench
+    q = dict(call="pair_backward", d=8, order=order)
+    timed, *warm = record([dict(q, lx=1_000_000, ly=1_000_000)] + [
+        dict(q, lx=nx, ly=ny, rows=kw.get("block_rows", 0), cols=kw.get("block_cols", 0))
+        for nx, ny, kw in bench.LONG_GRAD_WARMUP])
+    assert all(r["rc"] == 0 for r in [timed] + warm)
+    need = set(kernels(timed))
+    assert {"lines_kernel<%d,8>" % order, "bwd_kernel<%d,8>" % order} <= need
+    assert need <= {k for r in warm for k in kernels(r)}
+    assert max(r["bytes"] for r in warm) <= timed["bytes"]
