@@ -811,14 +811,11 @@ struct StripCtx {
                 return;
             }
         }
-        for (; t < te; ++t) {
-            if (ck && ((unsigned)t % (unsigned)ck_every) == 0) save_state(t);
-            step<QD>(t, stage);
-        }
+        for (; t < te; ++t) step<QD>(t, stage);
     }
 
     // Steps 0 .. T-1 of the strip.
-    __device__ bool run(int T) {
+    __device__ __forceinline__ bool run(int T) {
         const int m = g.m;
         int t = 0;
         while (t < T) {
@@ -837,6 +834,12 @@ struct StripCtx {
                 const int nxt = tc - (tc % TC) + TC - 1;
                 te = min(te, stage ? min(nxt, m - 1) + kWave : kWave - 1);
             }
+            if (ck) {
+                // (outside the specialised loops: a copy of the stores in each kept
+                // their arrays in memory from order 16, and at order 12 with d 32)
+                if (((unsigned)t % (unsigned)ck_every) == 0) save_state(t);
+                te = min(te, t - t % ck_every + ck_every);
+            }
             te = uniform(te);
             // (between the ramps a product: the general count's scalar arithmetic is
             // 2-4% of the time where a lone wave's steps are short)
@@ -854,8 +857,10 @@ struct StripCtx {
         return true;
     }
 
-    // Sweep the whole strip.  Returns false if abandoned (watchdog).
-    __device__ bool sweep() {
+    // Sweep the whole strip.  Returns false if abandoned (watchdog).  (Inlined in
+    // every kernel: as a call, which two kernels of one unit shared from order 16
+    // up, it kept the whole context in memory.)
+    __device__ __forceinline__ bool sweep() {
         const int lane = lane_id();
         const int m = g.m;
         const int row0 = s * kWave;
