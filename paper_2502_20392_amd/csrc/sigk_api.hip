@@ -490,9 +490,11 @@ constexpr int kBwdMaxGrid = 2048;
 
 // Whether an adjoint launch of this many strips runs two waves per strip: as
 // long as every wave has a SIMD to itself.  Measured one wave over two, at
-// orders 5-20 and d 3-32: 1.23-1.43 for 78 pairs of 100 points (156 strips) and
+// orders 5-16 and d 3-16: 1.23-1.43 for 78 pairs of 100 points (156 strips) and
 // 36 of 300 (180).
-bool bwd_two_waves(int64_t tickets) { return tickets <= 2 * device_cus(); }
+bool bwd_two_waves(int P, int D, int64_t tickets) {
+    return bwd_two_compiled(P, D) && tickets <= 2 * device_cus();
+}
 
 // Segment buffers the adjoint's recompute scratch is sized for: those of the
 // adjoint launch on the current device (two per strip of a two-wave launch,
@@ -503,15 +505,13 @@ int bwd_scratch_grid(int P, int D, int64_t tickets) {
     const int g = device_wgs(P, D, kKernelBwd);
     const int64_t n = g > 0 ? std::min(g, kBwdMaxGrid) : kBwdMaxGrid;
     const int64_t one = std::min<int64_t>(n, tickets);
-    return (int)std::max<int64_t>(bwd_two_waves(tickets) ? 2 * tickets : one, 1);
+    return (int)std::max<int64_t>(bwd_two_waves(P, D, tickets) ? 2 * tickets : one, 1);
 }
 
 // The adjoint launch over b.ntickets strips with `bufs` segment buffers.
 hipError_t launch_bwd(const Variant* v, const BwdArgs& b, int P, int D, int grid_opt, int bufs,
                       hipStream_t s) {
-    // (order 24 with d > 16 spills 600 registers there: 0.87 of the one-wave rate)
-    if (grid_opt <= 0 && bwd_two_waves(b.ntickets) && bufs >= 2 * b.ntickets &&
-        !(P > 20 && D > 16))
+    if (grid_opt <= 0 && bwd_two_waves(P, D, b.ntickets) && bufs >= 2 * b.ntickets)
         return v->bwd_two(b, (int)std::max<int64_t>(b.ntickets, 1), s);
     const int grid = grid_opt > 0 ? grid_opt : device_wgs(P, D, kKernelBwd);
     return v->bwd(b, (int)std::max<int64_t>(std::min<int64_t>(std::min(grid, bufs), b.ntickets), 1),

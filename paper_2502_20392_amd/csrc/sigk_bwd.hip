@@ -848,9 +848,17 @@ hipError_t SIGK_NAME(launch_bwd_, SIGK_P, SIGK_D)(const BwdArgs& b, int grid, hi
     return hipGetLastError();
 }
 
+template <int P, int D>
+hipError_t launch_two(const BwdArgs& b, int grid, hipStream_t s) {
+    if constexpr (bwd_two_compiled(P, D)) {
+        hipLaunchKernelGGL((bwd_two_kernel<P, D>), dim3(grid), dim3(2 * kWave), 0, s, b);
+        return hipGetLastError();
+    } else {
+        return hipErrorNotSupported;
+    }
+}
 hipError_t SIGK_NAME(launch_bwd_two_, SIGK_P, SIGK_D)(const BwdArgs& b, int grid, hipStream_t s) {
-    hipLaunchKernelGGL((bwd_two_kernel<SIGK_P, SIGK_D>), dim3(grid), dim3(2 * kWave), 0, s, b);
-    return hipGetLastError();
+    return launch_two<SIGK_P, SIGK_D>(b, grid, s);
 }
 
 int SIGK_NAME(occupancy_ckpt_, SIGK_P, SIGK_D)() {

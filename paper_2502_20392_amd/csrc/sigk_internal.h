@@ -111,6 +111,13 @@ __host__ __device__ constexpr int alt_chunk_cols(int P, int D) {
     return fwd_chunk_cols(P, D) == 64 ? 32 : 64;
 }
 
+// Adjoint variants compiled with two waves per strip as well.  Not where its halves
+// spill so much that one wave is faster: one over two, 8-64 pairs of 33-1000 points,
+// order 24 0.80-0.95, order 20 with d > 16 0.92-0.97 (order 20 with d <= 16 1.07-1.15).
+__host__ __device__ constexpr bool bwd_two_compiled(int P, int D) {
+    return P < 20 || (P == 20 && D <= 16);
+}
+
 // Per-pair geometry for table mode (ragged batches).  Offsets in elements.
 struct PairDesc {
     int64_t x_off;      // first double of path x in the pool

@@ -179,3 +179,13 @@ def test_benchmark_warms_every_kernel_of_the_long_gradient(order):
     assert {"lines_kernel<%d,8>" % order, "bwd_kernel<%d,8>" % order} <= need
     assert need <= {k for r in warm for k in kernels(r)}
     assert max(r["bytes"] for r in warm) <= timed["bytes"]
+
+
+def test_two_waves_per_strip_where_they_are_the_faster_adjoint():
+    """Few strips take two waves each, except at the orders whose halves spill."""
+    for order, d, want in ((5, 32, "two"), (16, 32, "two"), (20, 16, "two"), (20, 32, "one"),
+                           (24, 3, "one"), (24, 16, "one"), (24, 32, "one")):
+        r, = record([dict(call="plan", lens=[100] * 9, pairs=[[i, i + 1] for i in range(8)], d=d,
+                          order=order, steps=["backward"])])
+        names = {k.split("<")[0] for k in kernels(r)}
+        assert ("bwd_two_kernel" in names) == (want == "two"), (order, d, names)
