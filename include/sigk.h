@@ -31,7 +31,7 @@
  *     = the null stream).  No call allocates device memory or synchronises
  *     the device, except those marked "synchronous".
  *   - `ws` is a caller-owned device workspace of at least the size returned
- *     by the matching *_workspace_size call.  The library keeps no pointer
+ *     by the matching *_workspace_size call (sigk_pair_backward also takes less).  The library keeps no pointer
  *     after a call returns.  Two calls may not share a workspace concurrently.
  *   - Return value: SIGK_OK or a negative SIGK_E* code from host-side
  *     validation or the kernel launch.  Numerical warnings raised on the
@@ -92,14 +92,16 @@ typedef struct sigk_opts {
     int32_t order;     /* P = coefficients kept per edge series (degree P-1);
                           0 selects 12.  Rounded up to a compiled value
                           (4,5,6,8,10,12,16,20,24).                               */
-    int32_t grid;      /* persistent workgroups; 0 = fill the device              */
+    int32_t grid;      /* persistent workgroups; 0 = chosen per launch.  > 0 also
+                          asks for a strip per workgroup                        */
     uint32_t flags;    /* SIGK_FLAG_*                                              */
     int32_t tile_cols; /* work tile of the forward sweeps with d <= 32: 64 grid
-                          rows x tile_cols columns per frontier chunk.  0 = the
-                          compiled default for (order, d); the other compiled
-                          width (32 or 64) may be chosen, e.g. by an autotuner;
-                          any other value gives SIGK_EUNSUPPORTED.  The
-                          checkpointing and adjoint sweeps ignore it.           */
+                          rows x tile_cols columns per frontier chunk.  0 = chosen
+                          per launch: either compiled width, and for pair and Gram
+                          calls also teams of strips in one workgroup.  32 or 64
+                          asks for that width (a strip per workgroup), e.g. from an
+                          autotuner; any other value gives SIGK_EUNSUPPORTED.
+                          The checkpointing and adjoint sweeps ignore it.       */
 } sigk_opts;
 
 typedef struct sigk_counters {
@@ -331,8 +333,7 @@ int sigk_backward(const double* pool, int64_t pool_points, const int64_t* offset
 /* ---------------------------------------------------------------- long pair gradient */
 /*
  * k(x, y) and its gradient for ONE pair with block (two-level) checkpointing,
- * for pairs too long for per-strip checkpoints (memory of order
- * (lx + ly) P sqrt(lx ly) instead of lx ly P):
+ * for pairs too long for per-strip checkpoints:
  *   grad_x[i][c] += grad_out[0] dk/dx[i][c],  grad_y[j][c] += grad_out[0] dk/dy[j][c].
  * The derivative is the one sigk_backward computes (the exact adjoint of the
  * truncated cell maps, chained through c_kl = <dx_k, dy_l>; Sec. 2.1, Prop.
@@ -340,7 +341,8 @@ int sigk_backward(const double* pool, int64_t pool_points, const int64_t* offset
  *   1. one forward sweep of the whole pair, which writes k(x, y) and keeps
  *      the edge series on the boundaries of blocks of block_rows x block_cols
  *      cells (the top edges of every block row's last row, the right edges of
- *      every block column's last column);
+ *      every block column's last column); left out where one block holds the
+ *      pair, whose recomputed sweep in stage 2 then gives k(x, y);
  *   2. block anti-diagonal by anti-diagonal, from the top-right corner down:
  *      the forward sweep of each block recomputed from its boundary series
  *      with per-strip checkpoints, then its adjoint sweep, which takes the
@@ -349,12 +351,17 @@ int sigk_backward(const double* pool, int64_t pool_points, const int64_t* offset
  *   3. the chain to the points.
  * x: [lx][d], y: [ly][d] (device, FP64); d <= 32.  grad_out (device) [1].
  * k_out (device) [1] or NULL.  grad_x [lx][d], grad_y [ly][d] (device),
- * ACCUMULATED.  block_rows: a multiple of 64, block_cols >= 1; 0 chooses a
- * square block near sqrt(14.2 max(lx, ly)) (least workspace).  Truncation
- * warnings of the forward sweep go to the status word as for sigk_pair.
- * Allocates nothing, never synchronises.  ws: at least
- * sigk_pair_backward_workspace_size bytes (host, same sizes);
- * sigk_pair_backward_blocks (host) returns the block sizes used.
+ * ACCUMULATED.  Truncation warnings of the forward sweep go to the status word
+ * as for sigk_pair.  Allocates nothing, never synchronises.
+ * block_rows: a multiple of 64, block_cols >= 1; with 0 for both the call takes
+ * the largest square blocks whose workspace fits ws_bytes and 4 GiB (fewer, larger
+ * launches), down to those of least memory, of side sqrt(14.2 max(lx, ly)) in whole
+ * strips (memory of order (lx + ly) P sqrt(lx ly) instead of lx ly P).  A call whose
+ * ws_bytes is below those is refused with SIGK_EWORKSPACE before anything runs.
+ * sigk_pair_backward_workspace_size (host, same sizes) returns the recommended
+ * size, that of the blocks within 4 GiB, or with explicit blocks theirs (so the least
+ * size is that of block_rows = the side above); sigk_pair_backward_blocks (host)
+ * the block sizes used with it.
  */
 int sigk_pair_backward_workspace_size(int64_t lx, int64_t ly, int64_t d, int64_t block_rows,
                                       int64_t block_cols, const sigk_opts* o, size_t* bytes);

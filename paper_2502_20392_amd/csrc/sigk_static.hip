@@ -10,9 +10,10 @@
 //
 // All calls on one device share the array, so calls that overlap on a device
 // (different streams, or host threads without ordering) race on it.  The
-// reset kernel that starts every sigk_gram launch clears what must start at
-// zero (status, tickets, counters, progress flags); the frontier rows are
-// written before they are read.
+// reset kernel that starts every sigk_gram call of more than one strip clears what
+// must start at zero (status, tickets, counters, progress flags), and the wave of a
+// single strip sets what it reports itself; the frontier rows are written before
+// they are read.
 #include <hip/hip_runtime.h>
 
 #include <mutex>
