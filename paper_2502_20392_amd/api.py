@@ -802,7 +802,7 @@ class _GramFunction(torch.autograd.Function):
             G[jj, ii] = vals
         else:
             G.view(-1).copy_(vals)
-        ctx.pool, ctx.pairs, ctx.symmetric = pool, pairs, symmetric
+        ctx.pool, ctx.symmetric = pool, symmetric
         ctx.shapes = (X.shape, None if symmetric else Y.shape)
         return G
 

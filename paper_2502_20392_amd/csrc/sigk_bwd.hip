@@ -36,9 +36,9 @@
 namespace sigk {
 
 // Frontier chunk of the checkpointing forward sweep (which also sets the
-// granularity of the Neumann depths the adjoint reads back): 64 columns where
-// the kernel runs one wave per SIMD anyway (orders 10-20, D <= 16), as in the
-// plain forward sweep; 32 elsewhere.
+// granularity of the Neumann depths the adjoint reads back): 64 columns at orders
+// 10-20 with D <= 16, as in the plain forward sweep (this one runs a wave per SIMD
+// there); 32 elsewhere.
 template <int P, int D>
 constexpr int ckpt_chunk = (P >= 10 && P <= 20 && D <= 16) ? 64 : 32;
 
@@ -234,7 +234,7 @@ struct StripBwd {
     bool lane_ok, has_below, has_above;
     double dy[D];
     double gy[D];
-    Recip<P, false> R;  // scalar or rematerialised constants: registers are scarce here
+    Recip<P> R;  // scalar or rematerialised constants: registers are scarce here
     int dx_lo, lin_lo, bin_chunk;
     // kCkptEvery x P recomputed bottom-edge rows, then as many left-edge rows (a
     // smooth segment of the two-wave kernel: P rows of right edges after it);
@@ -330,7 +330,6 @@ struct StripBwd {
     // columns [c0, c1) are final: publish the bottom-edge cotangents to the
     // strip below and add dL/d(dx) to the path's gradient scratch
     __device__ void flush_cols(int c0, int c1) {
-        const int CH = ACH;
         const int lane = lane_id();
         wave_sync();
         const int nc = c1 - c0;
@@ -349,7 +348,6 @@ struct StripBwd {
                 L.gx(ch, sl) = 0.0;
             }
         }
-        (void)CH;
         wave_sync();
     }
 

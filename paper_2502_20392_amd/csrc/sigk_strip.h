@@ -57,12 +57,6 @@ __device__ __forceinline__ int ring_slot_of(int col) {
         return (int)((unsigned)(col + RB) % (unsigned)RB);
 }
 
-// The same for the adjoint's rings (ring_cols(P) columns).
-template <int P>
-__device__ __forceinline__ int ring_slot(int col) {
-    return ring_slot_of<ring_cols(P)>(col);
-}
-
 // Byte offset of a lane's slot in a ring of ARB columns, stepped one column
 // at a time (two or three vector instructions instead of a division).
 template <int ARB>
@@ -83,13 +77,13 @@ struct RingPos {
     }
 };
 
-// D > 0: the channel bucket (d <= D, increments in LDS and registers);
-// D = 0: the cell coefficients come from a field computed beforehand.
 // Columns per increment load and Neumann depth: 64 where a 128-column ring
 // serves 64-column chunks, else 32.
 template <int CH, int RB>
 constexpr int inc_chunk = RB >= 64 + kWave - 1 && CH == 64 ? 64 : 32;
 
+// D > 0: the channel bucket (d <= D, increments in LDS and registers);
+// D = 0: the cell coefficients come from a field computed beforehand.
 template <int P, int D, int CH, int RB, int TC = CH>
 struct LdsStrip {
     static_assert(RB >= 32 + kWave - 1 && CH % TC == 0,
@@ -110,19 +104,17 @@ struct Acc {
     unsigned status = 0;
 };
 
-// Reciprocals 1/k, k = 0..2P (entry 0 unused).  For mid-size P they are pinned
-// in vector registers (the wave runs alone on its SIMD there anyway), so the
-// hot loop neither rebuilds them nor spills them from scalar registers; for
-// small P the registers buy more occupancy instead.
-template <int P, bool kPinVector = false>
+// Reciprocals 1/k, k = 0..2P (entry 0 unused).  Up to order 12 they are pinned in
+// scalar registers, so that the hot loop does not rebuild them and the vector
+// registers hold edges (two waves per SIMD fit at orders 8-12 for it).
+template <int P>
 struct Recip {
     double v[2 * P + 1];
     __device__ __forceinline__ void init() {
 #pragma unroll
         for (int k = 0; k <= 2 * P; ++k) {
             v[k] = k == 0 ? 0.0 : 1.0 / (double)k;
-            if (kPinVector) asm volatile("" : "+v"(v[k]));
-            else if (P <= 12 && k > 2) asm volatile("" : "+s"(v[k]));
+            if (P <= 12 && k > 2) asm volatile("" : "+s"(v[k]));
         }
     }
     __device__ __forceinline__ double operator()(int k) const { return v[k]; }
@@ -311,12 +303,6 @@ __device__ __forceinline__ double wave_max_nn(double v) {
 __device__ __forceinline__ double wave_sum(double v) {
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o);
-    return v;
-}
-
-__device__ __forceinline__ double wave_min(double v) {
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v = fmin(v, __shfl_xor(v, o));
     return v;
 }
 
@@ -580,10 +566,11 @@ struct StripCtx {
     }
 
     // Load columns [c0, c0+XC) (increments, their norms, and at a chunk's start
-    // its bottom edges) and set the Neumann depth for steps [c0, c0+XC).  Columns past the last one are
-    // zero increments: a lane past the end of its row then maps with c = 0
-    // (nothing tallied) and the steps need no per-lane test.  A chunk with no
-    // column of the grid keeps the depth of the one before.
+    // its bottom edges) and set the Neumann depth for steps [c0, c0+XC).
+    // Columns past the last one are zero increments: a lane past the end of its
+    // row then maps with c = 0 (nothing tallied) and the steps need no per-lane
+    // test.  A chunk with no column of the grid keeps the depth of the one
+    // before.
     __device__ bool load_chunk(int c0) {
         if constexpr (D == 0) return load_chunk_field(c0);
         const int lane = lane_id();
@@ -715,7 +702,8 @@ struct StripCtx {
     // and past its last column it maps with c = 0; neither reaches a cell of
     // the grid.  (A separate ramp loop with a branch per Neumann term cost
     // short pairs 6-11%: 33 x 27 points at order 12 took 62.5 us against 56.2,
-    // eight paths of 128 points at order 10 227 us against 214.)  stage: the top lane's edge is staged (t >= 63).
+    // eight paths of 128 points at order 10 227 us against 214.)  stage: the top
+    // lane's edge is staged (t >= 63).
     template <int QC>
     __device__ __forceinline__ void step(int t, bool stage) {
         const int lane = lane_id();

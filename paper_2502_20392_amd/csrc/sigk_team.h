@@ -240,7 +240,7 @@ struct TeamService {
 };
 
 // ------------------------------------------------------------ compute waves
-template <int P, int D, bool SQ>
+template <int P, int D>
 struct TeamWave {
     static constexpr int SUB = team_sub<P>, EC = team_ec<P>, CB = D > 0 ? team_colb<D> : 1;
     // the next step's coefficient is formed a step ahead where registers allow
@@ -342,7 +342,7 @@ struct TeamWave {
             } else {
                 c = *(const double*)xp;
             }
-            SplitMap<P, QC, SQ> S;
+            SplitMap<P, QC> S;
             S.pre(B, c, Bn, R);
             tally(c, B);
             __builtin_amdgcn_sched_barrier(0);
@@ -369,7 +369,7 @@ struct TeamWave {
                 c = *(const double*)xp;
             tally(c, A);
             tally(c, B);
-            cell_map<P, SQ>(A, B, c, An, Bn, QC, R);
+            cell_map<P>(A, B, c, An, Bn, QC, R);
         }
 #pragma unroll
         for (int i = 0; i < P; ++i) {
@@ -535,7 +535,7 @@ constexpr int team_eu = P <= 6 && D <= 8 ? 3 : (P <= 10 && D <= 16 ? 2 : 1);
 template <int P, int D>
 constexpr int team_max_waves = team_eu<P, D> > 1 ? 4 : 3;
 
-template <int P, int D, bool SQ = false>
+template <int P, int D>
 __global__ void __launch_bounds__(kWave*(team_max_waves<P, D> + 1))
     __attribute__((amdgpu_waves_per_eu(team_eu<P, D>))) team_kernel(FwdArgs a) {
     extern __shared__ double team_smem[];
@@ -584,7 +584,7 @@ __global__ void __launch_bounds__(kWave*(team_max_waves<P, D> + 1))
             TeamService<P, D> S{a, g, tg};
             S.run(a.frontier + g.front, a.frontier + g.front, a.progress + g.prog, below, above);
         } else if (w < tg.nw) {
-            TeamWave<P, D, SQ> S(a, g, tg, acc);
+            TeamWave<P, D> S(a, g, tg, acc);
             S.s = tg.s0 + w;
             S.w = w;
             S.has_below = w > 0 || below;
