@@ -303,16 +303,25 @@ int team_waves(int P, int D, const sigk_opts& op, int64_t strips, int64_t npairs
     const double all1 = (double)(npairs * strips);
     const double cap_t = device_wgs(P, D, kKernelTeam + W), all_t = (double)(npairs * groups);
     const double f1 = slow(std::min(all1, cap1) / simds);
+    // Teams on a CU: of many pairs, which start together, the most on any; of a few
+    // pairs those that run at a time (they start a team's lags after one another).
     const double cus = simds / 4.0;
-    const double f_t = slow(std::min(std::ceil(all_t / cus), cap_t / cus) * (W + 1) / 4.0);
+    const bool few = npairs * 16 <= cus;
+    const double active =
+        few ? std::min(all_t, (double)npairs * (1.0 + sweep / (double)(W * lag))) : all_t;
+    const double per_cu = few ? std::max(active / cus, 1.0) : std::ceil(active / cus);
+    const double f_t = slow(std::min(per_cu, cap_t / cus) * (W + 1) / 4.0);
     // the one-wave kernel's chunk round trips, against its steps
     const double trips = P <= 8 ? 1.15 : P <= 12 ? 1.1 : 1.03;
     const double chain1 =
         trips * (sweep + (double)(strips - 1) * (one.cols + kWave - 1));
     const double chain_t = sweep + (double)(strips - 1) * lag;
     const double t1 = std::max(chain1 * (all1 <= cap1 ? f1 : 1.0), sweep * all1 / cap1 * f1);
-    const double t_t =
-        f_t * std::max(chain_t, std::ceil(all_t / cap_t) * (sweep + 0.5 * (W - 1) * lag));
+    // (200,001 points, order 5: 226 ms by teams, 288-297 by one-wave workgroups)
+    const double rounds =
+        all_t <= cap_t ? 1.0 : few ? all_t / cap_t : std::ceil(all_t / cap_t);
+    const double t_t = std::max(chain_t * (all_t <= cap_t ? f_t : 1.0),
+                                rounds * (sweep + 0.5 * (W - 1) * lag) * f_t);
     return t_t < 0.9 * t1 ? W : 0;
 }
 

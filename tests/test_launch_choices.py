@@ -189,3 +189,10 @@ def test_two_waves_per_strip_where_they_are_the_faster_adjoint():
                           order=order, steps=["backward"])])
         names = {k.split("<")[0] for k in kernels(r)}
         assert ("bwd_two_kernel" in names) == (want == "two"), (order, d, names)
+
+
+def test_teams_on_one_pair_of_thousands_of_strips():
+    """More teams than are resident, started one after another along one pair."""
+    got = [forward(r)[0].split("<")[0] for r in record([
+        dict(call="gram", nx=1, lx=n, d=8, order=5) for n in (20001, 100001, 200001, 1_000_000)])]
+    assert got == ["team_kernel", "team_kernel", "team_kernel", "fwd_kernel"], got
