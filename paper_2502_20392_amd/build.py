@@ -55,6 +55,8 @@ def _digest(paths, extra):
 # unchanged.  The adjoint units keep the default from order 16 up, where this
 # compiler's iterative scheduler fails on some of them.
 ILP_SCHED = ["-mllvm", "-amdgpu-sched-strategy=iterative-ilp"]
+# blocks reached by jumps only (loops among them) start at 64 bytes
+ALIGNED = ["-mllvm", "-align-all-nofallthru-blocks=6"]
 
 
 def _unit_flags(src, defs):
@@ -63,6 +65,10 @@ def _unit_flags(src, defs):
     if P is None:
         return []
     if src == "sigk_fwd.hip":
+        if (P, D) == (12, 8) and d.get("SIGK_ALT"):
+            # a lone wave waits for its instructions: the narrow tile's loops by
+            # chance of layout took 48.3-50.4 us on 33 x 27 points, aligned 48.6
+            return ILP_SCHED + ALIGNED
         return [] if (P <= 6 and D <= 8) else ILP_SCHED
     if src == "sigk_bwd.hip":
         # (order 5 with d 32: the adjoint of 512 pairs of 1000 points took 56 ms with
