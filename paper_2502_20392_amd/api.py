@@ -860,15 +860,9 @@ class _MMD2Function(torch.autograd.Function):
         ci, cj = np.meshgrid(np.arange(nx), np.arange(ny), indexing="ij")
         blocks = [np.stack([xi, xj], 1), np.stack([nx + yi, nx + yj], 1),
                   np.stack([ci.ravel(), nx + cj.ravel()], 1)]
-        def triangle(n):
-            # of a symmetric block's pairs i <= j (made on the device: a copy from the
-            # host would wait for the launches before it)
-            ii, jj = torch.triu_indices(n, n, device=X.device)
-            return torch.where(ii == jj, 1.0, 2.0).to(torch.float64) / (n * n)
-
-        weights = [lambda: triangle(nx), lambda: triangle(ny),
-                   lambda: torch.full((nx * ny,), -2.0 / (nx * ny), dtype=torch.float64,
-                                      device=X.device)]
+        weights = [np.where(xi == xj, 1.0, 2.0) / (nx * nx),
+                   np.where(yi == yj, 1.0, 2.0) / (ny * ny),
+                   np.full(nx * ny, -2.0 / (nx * ny))]
         need_x, need_y = X.requires_grad, Y.requires_grad
         use = [need_x, need_y, need_x or need_y]  # XX, YY, XY blocks with a gradient
         total = torch.zeros((), dtype=torch.float64, device=X.device)
@@ -888,7 +882,9 @@ class _MMD2Function(torch.autograd.Function):
                 vals = plan.run(pool)
             if tally is not None:
                 tally.add(plan.ws)
-            wt = torch.cat([x() for x, u in zip(weights, sel) if u])
+            # (pinned: a copy from ordinary memory waits for the launches before it)
+            w = np.concatenate([x for x, u in zip(weights, sel) if u])
+            wt = torch.from_numpy(w).pin_memory().to(X.device, non_blocking=True)
             total = total + (vals * wt).sum()
             if grad:
                 w_g = wt
